@@ -406,9 +406,11 @@ int iesh_timing(iesh_ctx* ctx, int32_t enable);
    since the last read; synchronises. */
 int iesh_timing_read(iesh_ctx* ctx, double* ms, int64_t* launches);
 /* Algorithmic work since iesh_timing was last called: the number of
-   Chebyshev terms summed over all propagated trajectory-steps (one
-   propagation of a trajectory costs 4 K n^2 N real flops for K terms) and
-   the number of trajectory-steps. */
+   products with the n x n coupling matrix summed over all propagated
+   trajectory-steps (Chebyshev terms; on the mixed path's interaction-picture
+   propagation the terms of its Taylor polynomial; K products of a
+   trajectory cost 4 K n^2 N real flops) and the number of
+   trajectory-steps. */
 int iesh_work(iesh_ctx* ctx, int64_t* sum_cheb_terms, int64_t* traj_steps);
 /* The same two sums for the trajectories of one bath-size class (model index
    cls), for per-class work: one propagation of a trajectory of that class

@@ -166,6 +166,12 @@ void choose_slabs(ClassDev& c, int precision) { set_slabs(c, widest_slab(c, prec
 int autotune_slabs(iesh_ctx* ctx, ClassDev& c) {
   const int prec = ctx->run.precision;
   const int widest = widest_slab(c, prec, 1 << 20);
+  // interaction-picture classes run this kernel for a few queued
+  // trajectories only: one-tile slabs spread those over the most work-groups
+  if (c.ips) {
+    set_slabs(c, 1);
+    return prop_prepare(c, prec) == hipSuccess ? IESH_OK : fail(ctx, IESH_EDEVICE, "propagation LDS attribute");
+  }
   if (widest <= 1 || c.n_traj < 64) {
     set_slabs(c, widest);
     return IESH_OK;
@@ -600,7 +606,12 @@ int enqueue_step(iesh_ctx* ctx, int record) {
   };
   auto prop = [&]() -> int {
     for (auto& c : ctx->cls)
-      if (c.n_traj) HIPTRY(ctx, timed(ctx, IESH_TIMER_PROP, [&] { return launch_prop(c, r.precision, s); }));
+      if (c.n_traj)
+        HIPTRY(ctx, timed(ctx, IESH_TIMER_PROP, [&] {
+                 if (!c.ips) return launch_prop(c, r.precision, s);
+                 const hipError_t e = launch_prop_ip(c, s);
+                 return e == hipSuccess ? launch_prop_queue(c, s) : e;
+               }));
     return IESH_OK;
   };
   int rc;
@@ -921,6 +932,7 @@ int iesh_create(const iesh_model_desc* models, int32_t n_models, const int32_t* 
     if (T == 0) continue;
     const int nd = c.md.ndof;
     const bool dense = d.kind == IESH_MODEL_DENSE;
+    c.b_stride = (size_t)n_pad * n_pad;
     if ((rc = dalloc(ctx, &c.eps, M)) || (rc = dalloc(ctx, &c.vbar, M)) ||
         (rc = dalloc(ctx, &c.x, (size_t)T * nd)) || (rc = dalloc(ctx, &c.v, (size_t)T * nd)) ||
         (rc = dalloc(ctx, &c.F, (size_t)T * nd)) ||
@@ -993,11 +1005,22 @@ int iesh_create(const iesh_model_desc* models, int32_t n_models, const int32_t* 
     }
     if (r.precision == IESH_FP64) {
       if ((rc = dalloc(ctx, &c.C64, (size_t)T * N * n_pad * 2)) ||
-          (rc = dalloc(ctx, &c.Bt, (size_t)T * n_pad * n_pad)))
+          (rc = dalloc(ctx, &c.Bt, (size_t)T * c.b_stride)))
         return bail(rc);
     } else {
+      if (!dense) {
+        // the interaction picture's M (f16 pairs) shares the buffer of B
+        c.b_stride = std::max(c.b_stride, (size_t)n_pad * 32 * ip_kblocks(n_pad));
+        if ((rc = dalloc(ctx, &c.ips, (size_t)T * kIpStride)) ||
+            (rc = dalloc(ctx, &c.ipv, (size_t)T * kIpPlanes * n_pad)) ||
+            (rc = dalloc(ctx, &c.chebq, (size_t)2 + T)))
+          return bail(rc);
+        if (ip_prepare(c) != hipSuccess)
+          return (fail(ctx, IESH_EDEVICE, "propagation LDS attribute"), bail(IESH_EDEVICE));
+        c.cheb_groups = 4 * ctx->n_cu;
+      }
       if ((rc = dalloc(ctx, &c.C32, (size_t)T * N * n_pad * 2)) ||
-          (rc = dalloc(ctx, &c.Bt32, (size_t)T * n_pad * n_pad)) ||
+          (rc = dalloc(ctx, &c.Bt32, (size_t)T * c.b_stride)) ||
           (rc = dalloc(ctx, &c.low, lowdin_scratch_elems(c))) ||
           (rc = dalloc(ctx, &c.defect, (size_t)T)))
         return bail(rc);

@@ -44,6 +44,21 @@ enum GeoSlot {
 // coefficients (re, im) starting at [8].
 enum ChebSlot { CHEB_C = 0, CHEB_INVR = 1, CHEB_K = 2, CHEB_RHO = 3, CHEB_COEF = 8 };
 
+// Interaction-picture propagation of the mixed path (k_eig.hip sets it up,
+// prop_ip.hpp applies it).  Per trajectory ips[] holds IP_SUB sub-intervals
+// (0: the trajectory takes the Chebyshev series of cheb[] instead), IP_TERMS
+// Taylor terms, IP_RANK columns of Z, IP_UNSCALE = 1/scale of the stored M,
+// then the R x R matrices D and -D (Z^T Z) D / 2; ipv[] holds planes of n_pad
+// floats: cos and sin of the phases before and after a sub-interval (each as
+// two floats, high and low part), and the columns of Z.
+constexpr int kIpMaxRank = 8;
+enum IpSlot { IP_SUB = 0, IP_TERMS = 1, IP_RANK = 2, IP_UNSCALE = 3, IP_D = 8, IP_F2 = 8 + 64 };
+constexpr int kIpStride = 8 + 2 * 64;
+enum IpPlane { IPV_PRE = 0, IPV_POST = 4, IPV_Z = 8 };
+constexpr int kIpPlanes = 8 + kIpMaxRank;
+// k-blocks of 32 columns in the stored M (f16 pairs, see prop_ip.hpp)
+__host__ __device__ constexpr int ip_kblocks(int n_pad) { return (n_pad + 31) / 32; }
+
 // Model constants passed by value to kernels.
 struct ModelDev {
   int kind;
@@ -119,7 +134,15 @@ struct ClassDev {
   double* geo = nullptr;    // [T][kGeoStride]
   double* cheb = nullptr;   // [T][kChebStride]
   double* Bt = nullptr;     // [T][n_pad/4][n_pad/16][64] v*D at the midpoint, MFMA A-tile order
-  float* Bt32 = nullptr;    // same in FP32 (mixed path)
+  float* Bt32 = nullptr;    // same in FP32 (mixed path), or M in f16 pairs (interaction picture)
+  size_t b_stride = 0;      // elements of Bt / Bt32 per trajectory
+  // interaction-picture propagation (mixed arrowhead classes, else nullptr)
+  float* ips = nullptr;     // [T][kIpStride]
+  float* ipv = nullptr;     // [T][kIpPlanes][n_pad]
+  int32_t* chebq = nullptr; // [2 + T] queue of the trajectories that take the Chebyshev
+                            // series this step: count, work-groups done, list
+  int cheb_groups = 0;      // most work-groups of the launch over that queue
+  int ip_waves = 0;         // waves (16-column tiles) per interaction-picture work-group
   double* gbuf = nullptr;   // [T][N][n_pad] hop probabilities (query mode)
   double* obs = nullptr;    // [records][T][IESH_N_OBS] (class-local records)
   double2* low = nullptr;   // Loewdin scratch (mixed path)
@@ -344,6 +367,12 @@ hipError_t launch_dense_step(const ClassDev& c, double dt, Counters* cnt, hipStr
 hipError_t launch_dense_query(const ClassDev& c, int t0, int nt, int mode, hipStream_t s);
 hipError_t launch_dense_init_thermal(const ClassDev& c, double kT, uint64_t seed, hipStream_t s);
 hipError_t launch_prop(const ClassDev& c, int precision, hipStream_t s);
+// interaction-picture propagation (prop_ip.hpp): ip_prepare picks the launch
+// shape of a class and reserves its LDS; launch_prop_queue (k_prop.hip) takes
+// the trajectories left to the Chebyshev series
+hipError_t ip_prepare(ClassDev& c);
+hipError_t launch_prop_ip(const ClassDev& c, hipStream_t s);
+hipError_t launch_prop_queue(const ClassDev& c, hipStream_t s);
 hipError_t launch_prop_taps(const ClassDev& c, int mode, double* taps, int tap_k, hipStream_t s);
 int prop_max_col_tiles(int precision);
 int hop_resident_groups(const ClassDev& c, int precision, int n_cu);

@@ -619,70 +619,17 @@ __device__ void load_bath(const ClassDev& c, EigLds& L) {
   __syncthreads();
 }
 
-// One step for one trajectory up to (not including) the propagation.
-// sub = -1: the whole step (midpoint geometry for the propagator, then the
-// end point); sub = j in [0, nsub): only the propagator of electronic
-// sub-step j, frozen at x_n + (j + 1/2)/nsub (x_{n+1} - x_n) for dt/nsub;
-// sub = -2: only the end point (after the sub-steps).
-__device__ void eig_step_one(const ClassDev& c, int t, double dt_run, int precision, Counters* cnt,
-                             int sub, int nsub, EigLds& L) {
+// Propagator of one trajectory as a Chebyshev series: the coupling matrix
+// B = vD in the propagation kernel's tile order, the Gershgorin interval of
+// A = diag(lambda) - iB and the series' coefficients.  mm holds the model at
+// the frozen geometry (held in L) with v-weighted gradients times vfac.
+__device__ void cheb_setup(const ClassDev& c, int t, const ModelAt& mm, double vfac, double dte,
+                           int precision, EigLds& L, Counters* cnt, bool count_step) {
   const int tid = threadIdx.x;
-  if (t >= live_slots(c) || (c.status[t] & kFreezeMask)) return;
-  const double dt = c.clock ? c.clock[2 * (size_t)t] : dt_run;  // this trajectory's step
   const ModelDev& md = c.md;
-  load_bath(c, L);
-  const int nd = md.ndof;
-  if (tid < nd) {
-    const int nu = tid;
-    double vh, xn, x;
-    if (c.path) {
-      // prescribed path (one coordinate): v over the step from the two end points
-      const double* pp = c.path + (size_t)c.gtraj[t] * c.path_len + c.path_n;
-      x = pp[0];
-      xn = pp[1];
-      vh = (xn - x) / dt;
-    } else {
-      x = c.x[(size_t)t * nd + nu];
-      const double v = c.v[(size_t)t * nd + nu], F = c.F[(size_t)t * nd + nu];
-      vh = v + 0.5 * dt * F / md.mass_dof[nu];
-      xn = x + dt * vh;
-    }
-    L.nuc[0][nu] = vh;
-    L.nuc[1][nu] = xn;
-    L.nuc[2][nu] = (sub >= 0) ? x + ((sub + 0.5) / nsub) * (xn - x) : 0.5 * (x + xn);
-  }
-  __syncthreads();
-  const double vh = L.nuc[0][0];
-  const double dte = (sub >= 0) ? dt / nsub : dt;  // electronic step of this propagator
-
   const int n = md.n, n_pad = md.n_pad, RT = n_pad / 16;
-  if (sub != -2) {
-  // ---- midpoint geometry: couplings for the propagator
-  // warm starts from the trajectory's previous solve (not along prescribed
-  // paths, whose backward pass revisits steps out of order)
-  const bool warm = c.root_tau && !c.path;
-  // the mixed path's step solves stop the secular iteration earlier (not
-  // along prescribed paths, whose gradients are FP64)
-  const double accept = (precision == IESH_FP64 || c.path) ? kStepAccept : kStepAcceptMixed;
-  RootStore rs{};
-  if (warm) rs = root_store(c, t);
-  ModelAt mm = solve_arrowhead(md, c.vbar, L.nuc[2], L, rs, warm, warm, accept);
-  double vfac = vh;
-  if (nd > 1) {
-    // v . D over the coordinates: the gradients enter through v.grad h and v.grad f / f
-    double dhe = 0.0, rhoe = 0.0;
-    for (int nu = 0; nu < nd; ++nu) {
-      double dh, rho, dU0;
-      multi_dof_grad(md, L.nuc[2], nu, dh, rho, dU0);
-      dhe += L.nuc[0][nu] * dh;
-      rhoe += L.nuc[0][nu] * rho;
-    }
-    mm.dh = dhe;
-    mm.rho = rhoe;
-    vfac = 1.0;
-  }
-  double* Bt = c.Bt + (size_t)t * n_pad * n_pad;
-  float* Bt32 = c.Bt32 ? c.Bt32 + (size_t)t * n_pad * n_pad : nullptr;
+  double* Bt = c.Bt + (size_t)t * c.b_stride;
+  float* Bt32 = c.Bt32 ? c.Bt32 + (size_t)t * c.b_stride : nullptr;
   double lo_part = 1e300, hi_part = -1e300;
   for (int k = tid; k < n; k += kEigThreads) L.eo[k] = L.e[L.org[k]];
   __syncthreads();
@@ -733,9 +680,349 @@ __device__ void eig_step_one(const ClassDev& c, int t, double dt_run, int precis
   }
   if (tid == 0) {
     double* cb = c.cheb + (size_t)t * kChebStride;
-    if (write_cheb(cb, L.red[0], L.red2[0], dte, precision, cnt, sub <= 0, L.J, c.work) < 0)
+    if (write_cheb(cb, L.red[0], L.red2[0], dte, precision, cnt, count_step, L.J, c.work) < 0)
       atomicOr(&L.fail, 2);
+    if (c.ips) {
+      c.ips[(size_t)t * kIpStride + IP_SUB] = 0.0f;
+      c.chebq[2 + atomicAdd(&c.chebq[0], 1)] = t;
+    }
   }
+}
+
+// Interaction-picture propagator of one trajectory (mixed path): with
+// A = Lambda - iB, B = vD, and t = dte / s,
+//   exp(-iA dte) = (E V E)^s,  E = exp(-i Lambda t / 2),
+// V the time-ordered exponential of -e^{i Lambda u} B e^{-i Lambda u} over
+// |u| <= t/2.  Its first two Magnus terms are kept in the form
+//   V = e^{S} e^{-M} e^{-S},  M_jk = t B_jk sinc((lambda_j - lambda_k) t / 2),
+//   S_jk = -(i/2) t B_jk j_1((lambda_j - lambda_k) t / 2),
+// M real and antisymmetric, and S = i (Z D Z^T - diag): B_jk (lambda_k -
+// lambda_j) = q0_j q0_k (a + b (mu_j + mu_k)) (mu = lambda - h) times
+// j_1(x)/x = (1/4) int_{-1}^{1} (1 - u^2) cos(x u) du, a Gauss rule of P node
+// pairs, gives 2P or (b != 0) 4P columns q0 cos(u mu t/2), q0 sin(..), and mu
+// times those.  The diagonal of S joins the phases.  ||M|| is small (the
+// electronic phases, which set the length of the Chebyshev series, are exact
+// here), so e^{-M} takes a Taylor polynomial of two to four terms.
+//
+// The plan (s, terms p, P) comes from the neglected terms: with beta >= ||M||
+// (Montgomery and Vaughan's inequality for sum x_j x_k / (lambda_j -
+// lambda_k), constant 1.3154 pi (Preissmann), over the gaps delta_j to the
+// nearest neighbour), nu = t^2 (|a| + 2|b| ||V||) and the spread ||V|| of
+// Lambda seen from the impurity, the third Magnus terms are below beta^2 nu t
+// ||V|| / 180 + beta nu^2 / 30 and the Gauss rule leaves 2 beta nu / 4 times
+// its weighted error; their sum may reach one FP32 rounding unit (2^-24; the
+// measured truncation is a fifth of the sum or less), the Taylor tail 2^-27.
+// A trajectory that needs more than three sub-intervals takes the Chebyshev
+// series.
+constexpr double kIpTol = 0x1p-24;
+constexpr double kIpTaylorTol = 0x1p-27;
+constexpr int kIpMaxSub = 3;
+constexpr int kIpMaxTerms = 8;
+// positive nodes and weights of the two- and four-point Gauss rules for
+// 1 - u^2 on [-1, 1]: sqrt(1/5); sqrt((7 -+ 2 sqrt 7) / 21), weights
+// (14 +- sqrt 7)/30 (1 - u^2)
+constexpr double kIpNode[2][2] = {{0.44721359549995794, 0.0}, {0.28523151648064510, 0.76505532392946469}};
+constexpr double kIpWeight[2][2] = {{2.0 / 3.0, 0.0}, {0.50971675, 0.15694991}};
+
+__device__ bool ip_setup(const ClassDev& c, int t, const ModelAt& mm, double vfac, double dte,
+                         EigLds& L, Counters* cnt, bool count_step) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const ModelDev& md = c.md;
+  const int n = md.n, n_pad = md.n_pad;
+  const double a = vfac * mm.dh, b = vfac * mm.rho, h = mm.h;
+  for (int k = tid; k < n; k += kEigThreads) L.eo[k] = L.e[L.org[k]];
+  __syncthreads();
+  // maxima of q0^2 / delta and (q0 mu)^2 / delta; ||V||^2 = sum q0^2 mu^2; the
+  // weighted squared errors of the two Gauss rules for s = 1 .. 3
+  double m1 = 0.0, m2 = 0.0, sv = 0.0, ge[2][kIpMaxSub] = {};
+  for (int j = tid; j < n; j += kEigThreads) {
+    const double q = L.q0[j];
+    if (q == 0.0) continue;
+    double gap = 1e300;
+    int k = j - 1;
+    while (k >= 0 && L.q0[k] == 0.0) --k;  // deflated states couple to nothing
+    if (k >= 0) gap = (L.eo[j] - L.eo[k]) + (L.tau[j] - L.tau[k]);
+    k = j + 1;
+    while (k < n && L.q0[k] == 0.0) ++k;
+    if (k < n) gap = fmin(gap, (L.eo[k] - L.eo[j]) + (L.tau[k] - L.tau[j]));
+    const double q2 = q * q, mu = L.lam[j] - h, rg = q2 / gap;
+    m1 = fmax(m1, rg);
+    m2 = fmax(m2, mu * mu * rg);
+    sv = fma(q2, mu * mu, sv);
+#pragma unroll
+    for (int s = 1; s <= kIpMaxSub; ++s) {
+      const double x = mu * dte * (1.0 / s), x2 = x * x, x4 = x2 * x2;
+      const double g1 = fmin(6.3e-4 * x4, 0.33), g2 = fmin(2.2e-8 * x4 * x4, 0.33);
+      ge[0][s - 1] = fma(q2, g1 * g1, ge[0][s - 1]);
+      ge[1][s - 1] = fma(q2, g2 * g2, ge[1][s - 1]);
+    }
+  }
+  double red[3 + 2 * kIpMaxSub] = {m1, m2, sv};
+#pragma unroll
+  for (int s = 0; s < kIpMaxSub; ++s) {
+    red[3 + s] = ge[0][s];
+    red[3 + kIpMaxSub + s] = ge[1][s];
+  }
+#pragma unroll
+  for (int q = 0; q < 3 + 2 * kIpMaxSub; ++q) {
+    for (int sh = 32; sh > 0; sh >>= 1) {
+      const double o = __shfl_xor(red[q], sh);
+      red[q] = q < 2 ? fmax(red[q], o) : red[q] + o;
+    }
+    if (lane == 0) L.red[q * (kEigThreads / 64) + wave] = red[q];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 3 + 2 * kIpMaxSub; ++q) {
+    double v = L.red[q * (kEigThreads / 64)];
+    for (int w = 1; w < kEigThreads / 64; ++w) {
+      const double o = L.red[q * (kEigThreads / 64) + w];
+      v = q < 2 ? fmax(v, o) : v + o;
+    }
+    red[q] = v;
+  }
+  // the plan (the same in every thread)
+  const double vn = sqrt(red[2]);
+  const double bn = 1.3154 * 3.14159265358979324 * (fabs(a) * red[0] + 2.0 * fabs(b) * sqrt(red[0] * red[1]));
+  const double nn = fabs(a) + 2.0 * fabs(b) * vn;
+  int sub = 0, pairs = 1;
+#pragma unroll
+  for (int s = 1; s <= kIpMaxSub; ++s)
+#pragma unroll
+    for (int P = 1; P <= 2; ++P) {
+      if (sub) continue;
+      const double ts = dte / s, be = ts * bn, nu = ts * ts * nn;
+      const double eta = sqrt(2.0 * red[P == 1 ? 2 + s : 2 + kIpMaxSub + s]);
+      const double err = s * be * (be * nu * ts * vn * (1.0 / 180.0) + nu * nu * (1.0 / 30.0) + 0.5 * nu * eta);
+      if (be < 0.3 && err <= kIpTol) {
+        sub = s;
+        pairs = P;
+      }
+    }
+  if (!sub) return false;  // also for values that are not finite
+  const double ts = dte / sub, be = ts * bn;
+  int p = 1;
+  for (double term = 0.5 * be * be; sub * term > kIpTaylorTol && p < kIpMaxTerms; ++p) term *= be / (p + 2);
+  const int per = b != 0.0 ? 4 : 2, R = per * pairs;
+  // scale of M (a power of two): its elements are at most beta
+  int ex = 0;
+  frexp(fmax(be, 1e-30), &ex);
+  const double scale = ldexp(1.0, 14 - ex);
+
+  // phases, columns of Z, and the sines and cosines that M is built from
+  double* sn = L.Vh2;
+  double* cs = L.V2;
+  float* ipv = c.ipv + (size_t)t * kIpPlanes * n_pad;
+  float gram[kIpMaxRank * (kIpMaxRank + 1) / 2] = {};
+  const double rpi = 0.318309886183790672;  // 1 / pi
+  for (int j = tid; j < n_pad; j += kEigThreads) {
+    double pc = 1.0, ps = 0.0, qc = 1.0, qs = 0.0;
+    float z[kIpMaxRank] = {};
+    if (j < n) {
+      const double q = L.q0[j], mu = L.lam[j] - h, hl = 0.5 * ts * L.lam[j];
+      const double dg = ts * ts * (1.0 / 12.0) * q * q * fma(2.0 * b, mu, a);
+      sincospi((dg - hl) * rpi, &ps, &pc);
+      sincospi((-dg - hl) * rpi, &qs, &qc);
+      double s1, c1;
+      sincospi(0.5 * ts * mu * rpi, &s1, &c1);
+      sn[j] = s1;
+      cs[j] = c1;
+#pragma unroll
+      for (int P = 0; P < 2; ++P)
+        if (P < pairs) {
+          sincospi(0.5 * ts * mu * rpi * kIpNode[pairs - 1][P], &s1, &c1);
+          const float zc = (float)(q * c1), zs = (float)(q * s1);
+          if (per == 2) {
+            z[2 * P] = zc;
+            z[2 * P + 1] = zs;
+          } else {
+            z[4 * P] = zc;
+            z[4 * P + 1] = zs;
+            z[4 * P + 2] = (float)mu * zc;
+            z[4 * P + 3] = (float)mu * zs;
+          }
+        }
+    }
+    auto put = [&](int plane, double cosine, double sine) {  // high and low parts
+      const float ch = (float)cosine, sh = (float)sine;
+      float* at = ipv + (size_t)plane * n_pad + j;
+      at[0] = ch;
+      at[n_pad] = sh;
+      at[2 * n_pad] = (float)(cosine - (double)ch);
+      at[3 * n_pad] = (float)(sine - (double)sh);
+    };
+    put(IPV_PRE, pc, ps);
+    put(IPV_POST, qc, qs);
+#pragma unroll
+    for (int f = 0; f < kIpMaxRank; ++f)
+      if (f < R) {
+        ipv[(size_t)(IPV_Z + f) * n_pad + j] = z[f];
+#pragma unroll
+        for (int g = 0; g <= f; ++g) gram[f * (f + 1) / 2 + g] = fmaf(z[f], z[g], gram[f * (f + 1) / 2 + g]);
+      }
+    c.lam_mid[(size_t)t * n_pad + j] = (j < n) ? L.lam[j] : 0.0;
+  }
+  // Z^T Z over the work-group
+  float* gw = reinterpret_cast<float*>(L.red2);
+  constexpr int kG = kIpMaxRank * (kIpMaxRank + 1) / 2;
+#pragma unroll
+  for (int f = 0; f < kIpMaxRank; ++f)
+    if (f < R) {
+#pragma unroll
+      for (int g = 0; g <= f; ++g) {
+        float v = gram[f * (f + 1) / 2 + g];
+        for (int sh = 32; sh > 0; sh >>= 1) v += __shfl_xor(v, sh);
+        if (lane == 0) gw[wave * kG + f * (f + 1) / 2 + g] = v;
+      }
+    }
+  __syncthreads();  // also sn, cs
+  float* ips = c.ips + (size_t)t * kIpStride;
+  if (tid < R * R) {
+    const int f = tid / R, g = tid - f * R;
+    // D couples columns of one node pair: cos with cos, sin with sin
+    auto D = [&](int x, int y) -> float {
+      if (x / per != y / per || (x & 1) != (y & 1)) return 0.0f;
+      const int mx = (x % per) >> 1, my = (y % per) >> 1;
+      const float w = (float)(ts * ts * 0.125 * kIpWeight[pairs - 1][x / per]);
+      return mx + my == 0 ? w * (float)a : mx + my == 1 ? w * (float)b : 0.0f;
+    };
+    auto G = [&](int x, int y) -> float {
+      const int i = x >= y ? x * (x + 1) / 2 + y : y * (y + 1) / 2 + x;
+      float v = 0.0f;
+      for (int w = 0; w < kEigThreads / 64; ++w) v += gw[w * kG + i];
+      return v;
+    };
+    float f2 = 0.0f;
+    for (int x = 0; x < R; ++x) {
+      const float d = D(f, x);
+      if (d == 0.0f) continue;
+      for (int y = 0; y < R; ++y) {
+        const float e = D(y, g);
+        if (e != 0.0f) f2 = fmaf(d * G(x, y), e, f2);
+      }
+    }
+    ips[IP_D + tid] = D(f, g);
+    ips[IP_F2 + tid] = -0.5f * f2;
+  }
+  if (tid == 0) {
+    ips[IP_SUB] = (float)sub;
+    ips[IP_TERMS] = (float)p;
+    ips[IP_RANK] = (float)R;
+    ips[IP_UNSCALE] = (float)(1.0 / scale);
+    const unsigned long long products = (unsigned long long)(sub * p);
+    atomicAdd((unsigned long long*)&cnt->sum_cheb, products);
+    if (count_step) atomicAdd((unsigned long long*)&cnt->traj_steps, 1ull);
+    if (c.work) {
+      atomicAdd((unsigned long long*)&c.work[0], products);
+      if (count_step) atomicAdd((unsigned long long*)&c.work[1], 1ull);
+    }
+  }
+  // scale M in f16 pairs (hi + lo, 22 bits), in the propagation kernel's
+  // operand order [row tile][32 columns][hi, lo][lane][8]: a thread makes the
+  // 32 columns of a k-block for one row, eight to a store.
+  const int KB = ip_kblocks(n_pad);
+  typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+  h8* Mt = reinterpret_cast<h8*>(c.Bt32 + (size_t)t * c.b_stride);
+  const double sa = 2.0 * scale * a, sb = 2.0 * scale * b;
+  for (int idx = tid; idx < n_pad * KB; idx += kEigThreads) {
+    const int kb = idx / n_pad, j = idx - kb * n_pad;
+    const bool row = j < n;
+    const double qj = row ? L.q0[j] : 0.0, muj = row ? L.lam[j] - h : 0.0;
+    const double aj = qj * fma(sb, muj, sa), bj = qj * sb;
+    const double eoj = row ? L.eo[j] : 0.0, tj = row ? L.tau[j] : 0.0;
+    const double sj = row ? sn[j] : 0.0, cj = row ? cs[j] : 0.0;
+    const size_t base = ((size_t)((j >> 4) * KB + kb) * 2) * 64 + (j & 15);
+#pragma unroll 1
+    for (int g = 0; g < 4; ++g) {
+      h8 hi, lo;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int k = kb * 32 + ((i & 4) << 2) + 4 * g + (i & 3);
+        double val = 0.0;
+        if (k < n) {
+          const double num = L.q0[k] * fma(bj, L.lam[k] - h, aj);
+          const double dif = (L.eo[k] - eoj) + (L.tau[k] - tj);  // lambda_k - lambda_j
+          const double r = rcp_nr1(dif);
+          const double sd = fma(sn[k], cj, -cs[k] * sj);  // sin(dif t / 2)
+          val = (num == 0.0 || k == j) ? 0.0 : num * sd * (r * r);
+        }
+        const float v = (float)val;
+        hi[i] = (_Float16)v;
+        lo[i] = (_Float16)(v - (float)hi[i]);
+      }
+      Mt[base + 16 * g] = hi;
+      Mt[base + 64 + 16 * g] = lo;
+    }
+  }
+  return true;
+}
+
+// One step for one trajectory up to (not including) the propagation.
+// sub = -1: the whole step (midpoint geometry for the propagator, then the
+// end point); sub = j in [0, nsub): only the propagator of electronic
+// sub-step j, frozen at x_n + (j + 1/2)/nsub (x_{n+1} - x_n) for dt/nsub;
+// sub = -2: only the end point (after the sub-steps).
+template <bool kIp>
+__device__ void eig_step_one(const ClassDev& c, int t, double dt_run, int precision, Counters* cnt,
+                             int sub, int nsub, EigLds& L) {
+  const int tid = threadIdx.x;
+  if (t >= live_slots(c) || (c.status[t] & kFreezeMask)) return;
+  const double dt = c.clock ? c.clock[2 * (size_t)t] : dt_run;  // this trajectory's step
+  const ModelDev& md = c.md;
+  load_bath(c, L);
+  const int nd = md.ndof;
+  if (tid < nd) {
+    const int nu = tid;
+    double vh, xn, x;
+    if (c.path) {
+      // prescribed path (one coordinate): v over the step from the two end points
+      const double* pp = c.path + (size_t)c.gtraj[t] * c.path_len + c.path_n;
+      x = pp[0];
+      xn = pp[1];
+      vh = (xn - x) / dt;
+    } else {
+      x = c.x[(size_t)t * nd + nu];
+      const double v = c.v[(size_t)t * nd + nu], F = c.F[(size_t)t * nd + nu];
+      vh = v + 0.5 * dt * F / md.mass_dof[nu];
+      xn = x + dt * vh;
+    }
+    L.nuc[0][nu] = vh;
+    L.nuc[1][nu] = xn;
+    L.nuc[2][nu] = (sub >= 0) ? x + ((sub + 0.5) / nsub) * (xn - x) : 0.5 * (x + xn);
+  }
+  __syncthreads();
+  const double vh = L.nuc[0][0];
+  const double dte = (sub >= 0) ? dt / nsub : dt;  // electronic step of this propagator
+
+  const int n_pad = md.n_pad;
+  if (sub != -2) {
+  // ---- midpoint geometry: couplings for the propagator
+  // warm starts from the trajectory's previous solve (not along prescribed
+  // paths, whose backward pass revisits steps out of order)
+  const bool warm = c.root_tau && !c.path;
+  // the mixed path's step solves stop the secular iteration earlier (not
+  // along prescribed paths, whose gradients are FP64)
+  const double accept = (precision == IESH_FP64 || c.path) ? kStepAccept : kStepAcceptMixed;
+  RootStore rs{};
+  if (warm) rs = root_store(c, t);
+  ModelAt mm = solve_arrowhead(md, c.vbar, L.nuc[2], L, rs, warm, warm, accept);
+  double vfac = vh;
+  if (nd > 1) {
+    // v . D over the coordinates: the gradients enter through v.grad h and v.grad f / f
+    double dhe = 0.0, rhoe = 0.0;
+    for (int nu = 0; nu < nd; ++nu) {
+      double dh, rho, dU0;
+      multi_dof_grad(md, L.nuc[2], nu, dh, rho, dU0);
+      dhe += L.nuc[0][nu] * dh;
+      rhoe += L.nuc[0][nu] * rho;
+    }
+    mm.dh = dhe;
+    mm.rho = rhoe;
+    vfac = 1.0;
+  }
+  bool ip = false;
+  if constexpr (kIp) ip = c.ips && !c.path && ip_setup(c, t, mm, vfac, dte, L, cnt, sub <= 0);
+  if (!ip) cheb_setup(c, t, mm, vfac, dte, precision, L, cnt, sub <= 0);
   __syncthreads();
   }
   if (sub >= 0) {
@@ -783,20 +1070,22 @@ __device__ void eig_step_one(const ClassDev& c, int t, double dt_run, int precis
 __global__ __launch_bounds__(kEigThreads) __attribute__((amdgpu_waves_per_eu(kEigWavesPerSimd))) void k_eig_step(ClassDev c, double dt_run, int precision,
                                                            Counters* cnt, int sub, int nsub) {
   __shared__ EigLds L;
-  eig_step_one(c, blockIdx.x, dt_run, precision, cnt, sub, nsub, L);
+  eig_step_one<false>(c, blockIdx.x, dt_run, precision, cnt, sub, nsub, L);
 }
 
 // The same step for several arrowhead classes in one launch: block b works
 // on slot b - first[k] of class k (first[k] <= b < first[k + 1]).  The classes
 // come largest first, so the dispatcher hands out the long work-groups
 // first and the small classes fill the compute units behind them.
+// kIp: the mixed path, whose trajectories propagate in the interaction picture.
+template <bool kIp>
 __global__ __launch_bounds__(kEigThreads) __attribute__((amdgpu_waves_per_eu(kEigWavesPerSimd))) void k_eig_fused(ClassSet set, double dt_run, int precision,
                                                             Counters* cnt, int sub, int nsub) {
   __shared__ EigLds L;
   const int b = blockIdx.x;
   int k = 0;
   while (k + 1 < set.n && b >= set.first[k + 1]) ++k;
-  eig_step_one(set.c[k], b - set.first[k], dt_run, precision, cnt, sub, nsub, L);
+  eig_step_one<kIp>(set.c[k], b - set.first[k], dt_run, precision, cnt, sub, nsub, L);
 }
 
 // Eigen-solve at the current x (no dynamics): energies, amplitudes, model
@@ -1209,8 +1498,12 @@ hipError_t launch_eig_step(const ClassDev& c, double dt, Counters* cnt, hipStrea
 hipError_t launch_eig_fused(const ClassSet& set, double dt, int precision, Counters* cnt, hipStream_t s,
                             int sub, int nsub) {
   if (set.n < 1 || set.first[set.n] < 1) return hipSuccess;
-  hipLaunchKernelGGL(k_eig_fused, dim3(set.first[set.n]), dim3(kEigThreads), 0, s, set, dt, precision, cnt,
-                     sub, nsub);
+  if (precision == IESH_FP64)
+    hipLaunchKernelGGL(k_eig_fused<false>, dim3(set.first[set.n]), dim3(kEigThreads), 0, s, set, dt, precision,
+                       cnt, sub, nsub);
+  else
+    hipLaunchKernelGGL(k_eig_fused<true>, dim3(set.first[set.n]), dim3(kEigThreads), 0, s, set, dt, precision,
+                       cnt, sub, nsub);
   return hipGetLastError();
 }
 

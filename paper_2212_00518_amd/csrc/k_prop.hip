@@ -31,6 +31,7 @@
 // trajectory land on the same XCD and share B in L2.
 
 #include "iesh_internal.hpp"
+#include "prop_ip.hpp"
 
 namespace iesh {
 namespace {
@@ -279,14 +280,8 @@ __device__ void clenshaw_tiles(const Slab<T>& s, int t0, int tid) {
 // few tiers so that narrow slabs get a kernel with fewer registers (more
 // work-groups per CU).
 template <typename T, int kMode, int kQ>
-__device__ void prop_item(const ClassDev& c, T* taps, int tap_k, int b, unsigned char* smem_raw) {
+__device__ void prop_item(const ClassDev& c, T* taps, int tap_k, int t, int slab, unsigned char* smem_raw) {
   typedef PropCfg<T> Cfg;
-
-  // XCD-aware id mapping: blocks b, b+8, b+16, ... share an XCD.
-  const int xcd = b & 7;
-  const int local = b >> 3;
-  const int slab = local % c.n_slabs;
-  const int t = (local / c.n_slabs) * 8 + xcd;
   if (t >= live_slots(c)) return;
   if (c.status[t] & kFreezeMask) return;
 
@@ -306,7 +301,7 @@ __device__ void prop_item(const ClassDev& c, T* taps, int tap_k, int b, unsigned
   s.X0 = reinterpret_cast<T*>(smem_raw);
   s.X1 = s.X0 + (size_t)s.n_pad * s.ldx;
   s.lam = s.X1 + (size_t)s.n_pad * s.ldx;
-  s.Bt = Cfg::B(c) + (size_t)t * s.n_pad * s.n_pad;
+  s.Bt = Cfg::B(c) + (size_t)t * c.b_stride;
   T* Cg = Cfg::C(c) + (size_t)t * s.N * s.n_pad * 2;
   s.Cg = Cg;
   s.cb = c.cheb + (size_t)t * kChebStride;
@@ -403,7 +398,27 @@ __device__ void prop_item(const ClassDev& c, T* taps, int tap_k, int b, unsigned
 template <typename T, int kMode, int kQ>
 __global__ __launch_bounds__(kPropThreads) void k_prop(ClassDev c, T* taps, int tap_k) {
   extern __shared__ unsigned char smem_raw[];
-  prop_item<T, kMode, kQ>(c, taps, tap_k, blockIdx.x, smem_raw);
+  // XCD-aware id mapping: blocks b, b+8, b+16, ... share an XCD.
+  const int local = blockIdx.x >> 3;
+  prop_item<T, kMode, kQ>(c, taps, tap_k, (local / c.n_slabs) * 8 + (blockIdx.x & 7), local % c.n_slabs, smem_raw);
+}
+
+// Classes on the interaction picture queue the few trajectories that need
+// the series (c.chebq): their items are dealt to a launch of fixed size, and
+// the last work-group to finish resets the queue for the next propagator.
+template <int kQ>
+__global__ __launch_bounds__(kPropThreads) void k_prop_queue(ClassDev c) {
+  extern __shared__ unsigned char smem_raw[];
+  const int items = c.chebq[0] * c.n_slabs;
+  for (int i = blockIdx.x; i < items; i += gridDim.x) {
+    prop_item<float, kPropagate, kQ>(c, nullptr, 0, c.chebq[2 + i / c.n_slabs], i % c.n_slabs, smem_raw);
+    __syncthreads();
+  }
+  __syncthreads();
+  if (threadIdx.x == 0 && atomicAdd(&c.chebq[1], 1) == (int)gridDim.x - 1) {
+    c.chebq[0] = 0;
+    c.chebq[1] = 0;
+  }
 }
 
 template <typename T>
@@ -428,7 +443,16 @@ struct Tiers<float> {
 };
 
 template <typename T, int kMode>
-const void* prop_fn(int tier) {
+const void* prop_fn(int tier) {  // kMode -1: the queue kernel
+  if constexpr (kMode < 0) {
+    switch (tier) {
+      case 0: return (const void*)k_prop_queue<Tiers<T>::q[0]>;
+      case 1: return (const void*)k_prop_queue<Tiers<T>::q[1]>;
+      case 2: return (const void*)k_prop_queue<Tiers<T>::q[2]>;
+      default: return (const void*)k_prop_queue<Tiers<T>::q[3]>;
+    }
+  } else
+
   switch (tier) {
     case 0: return (const void*)k_prop<T, kMode, Tiers<T>::q[0]>;
     case 1: return (const void*)k_prop<T, kMode, Tiers<T>::q[1]>;
@@ -494,7 +518,7 @@ hipError_t prop_prepare(const ClassDev& c, int precision) {
       fns[1] = prop_fn<double, kClenshawTaps>(tier);
       fns[2] = prop_fn<double, kForwardTaps>(tier);
     } else {
-      fns[0] = prop_fn<float, kPropagate>(tier);
+      fns[0] = c.ips ? prop_fn<float, -1>(tier) : prop_fn<float, kPropagate>(tier);
     }
     for (const void* fn : fns) {
       if (!fn) continue;
@@ -512,6 +536,39 @@ hipError_t launch_prop(const ClassDev& c, int precision, hipStream_t s) {
   const size_t lds = prop_lds_bytes(c, precision);
   if (precision == IESH_FP64) return launch_prop_t<double, kPropagate>(c, grid, lds, s, nullptr, 0);
   return launch_prop_t<float, kPropagate>(c, grid, lds, s, nullptr, 0);
+}
+
+// The interaction picture: the 16-column tiles of a trajectory over
+// work-groups of equal width, as wide as the register file holds (at M = 200
+// two work-groups of seven waves take 1.26 ms per step, four of four 1.35,
+// seven of two 2.1: the work-groups of a trajectory each stream M).
+hipError_t ip_prepare(ClassDev& c) {
+  const int rt = c.md.n_pad / 16, tiles = (c.md.N + 7) / 8, most = prop_ip::max_waves(rt);
+  const int groups = (tiles + most - 1) / most;
+  c.ip_waves = (tiles + groups - 1) / groups;
+  return prop_ip::dispatch(rt, prop_ip::Launch{&c, dim3(1), 0, 0, nullptr, true});
+}
+
+hipError_t launch_prop_ip(const ClassDev& c, hipStream_t s) {
+  if (c.n_live < 1) return hipSuccess;
+  const int tiles = (c.md.N + 7) / 8, groups = (tiles + c.ip_waves - 1) / c.ip_waves;
+  const dim3 grid((c.n_live + 7) / 8 * 8 * groups);
+  return prop_ip::dispatch(c.md.n_pad / 16, prop_ip::Launch{&c, grid, 64 * c.ip_waves, groups, s, false});
+}
+
+// The queued trajectories of an interaction-picture class.
+hipError_t launch_prop_queue(const ClassDev& c, hipStream_t s) {
+  if (c.n_live < 1) return hipSuccess;
+  const int items = c.n_live * c.n_slabs;
+  const dim3 grid(c.cheb_groups < items ? c.cheb_groups : items);
+  const size_t lds = prop_lds_bytes(c, IESH_MIXED);
+  switch (prop_tier<float>(c)) {
+    case 0: hipLaunchKernelGGL((k_prop_queue<Tiers<float>::q[0]>), grid, dim3(kPropThreads), lds, s, c); break;
+    case 1: hipLaunchKernelGGL((k_prop_queue<Tiers<float>::q[1]>), grid, dim3(kPropThreads), lds, s, c); break;
+    case 2: hipLaunchKernelGGL((k_prop_queue<Tiers<float>::q[2]>), grid, dim3(kPropThreads), lds, s, c); break;
+    default: hipLaunchKernelGGL((k_prop_queue<Tiers<float>::q[3]>), grid, dim3(kPropThreads), lds, s, c); break;
+  }
+  return hipGetLastError();
 }
 
 // FP64 tap modes for the adjoint: mode 1 stores the Clenshaw vectors b_K .. b_1

@@ -1,0 +1,85 @@
+"""The mixed path's propagator over its plans and tile edges.
+
+One step from random orthonormal orbitals against the oracle's exponential.
+The ensemble's velocities run from rest to two hundred times thermal, so one
+launch holds the plans of the interaction picture (one to three sub-intervals,
+two to eight low-rank columns, one to many Taylor terms) and the trajectories
+that take the Chebyshev series.
+
+Tolerance, absolute on coefficients of modulus at most one: rounding the
+orbitals to FP32 at the upload, the phases before and after each of up to three
+sub-intervals (two roundings of 2^-24 each), the products' 2^-21 of ||M|| < 0.3
+per sub-interval and the truncation of at most 2^-24: below 1e-6.  The
+Chebyshev series rounds in each of its up to 60 terms: 4e-6.
+"""
+import numpy as np
+import pytest
+
+from oracle import dynamics as dyn, models
+from test_gpu_parity import ensemble, gpu, make_cfg, random_states, upload  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+FACTORS = np.array([0.0, 1e-3, 0.2, 0.7, 1.3, 2.5, 5.0, 9.0, 15.0, 30.0, 60.0, 200.0])
+
+
+# row tiles 1, 2, 3, 6, 7, 8, 12, 13, 14, 17, 21 (full and one row over), odd
+# and single orbital tiles, both baths, one and six coordinates, repeated levels
+@pytest.mark.parametrize("name,M,N", [
+    ("c1", 1, 1), ("c1", 15, 8), ("c2", 16, 9), ("c2gl", 46, 17), ("c2", 95, 48), ("c3", 96, 41),
+    ("c2", 127, 20), ("c3", 190, 95), ("c2", 200, 100), ("c2gl", 208, 104), ("c2", 223, 30),
+    ("c5", 256, 128), ("c5", 20, 7), ("c3", 320, 160), ("c1", 335, 168),
+])
+def test_mixed_step_over_plans_and_tiles(name, M, N):
+    cfg = make_cfg(name, M=M, N=N)
+    m = models.from_config(cfg, M=M)
+    T = len(FACTORS)
+    nd = m.n_dof
+    rs = np.random.default_rng(M)
+    xs = np.linspace(3.0, 9.0, T) if name == "c3" else np.linspace(-4.0, 10.0, T)
+    vth = 2e-3 if name == "c3" else 7e-4
+    states = random_states(m, N, T, seed=5 + M, xs=xs, v_scale=0.0)
+    for t, s in enumerate(states):
+        if nd > 1:
+            dof = np.array(cfg["model"]["dof"])
+            s.x = dof[:, 3] + 0.1 * rs.normal(size=nd)
+            s.v = FACTORS[t] * vth * rs.normal(size=nd)
+        else:
+            s.v[0] = FACTORS[t] * vth * (1 if t % 2 else -1)
+    ens = ensemble(cfg, T, precision="mixed")
+    upload(ens, states)
+    ens.step()
+    x, v, Cf, occ = ens.get_state()
+    status = ens.status()
+    from paper_2212_00518_amd import unpack_C
+    ok = 0
+    for t in range(T):
+        if status[t]:  # the series did not converge within its terms
+            assert FACTORS[t] >= 30.0
+            continue
+        F = dyn.el.forces(m, states[t].x, states[t].s)
+        ref = dyn.step(m, states[t], cfg["dt"], 2.0, F)[0]
+        err = np.max(np.abs(unpack_C(Cf, t, m.n, N, ens.n_max, ens.N_max) - ref.C))
+        print(f"{name} M={M} v x {FACTORS[t]}: |dC| {err:.2e}", flush=True)
+        assert err <= (1e-6 if FACTORS[t] < 9.0 else 4e-6), (t, err)
+        ok += 1
+    assert ok >= 8
+    ens.close()
+
+
+def test_mixed_propagator_product_counts():
+    """At rest one product per step is enough, a thermal trajectory takes two
+    to four, and a fast one the Chebyshev series' (eight at M = 200)."""
+    counts = {}
+    for f in (0.0, 1.0, 60.0):
+        cfg = make_cfg("c2", M=200, N=100)
+        ens = ensemble(cfg, 1, precision="mixed")
+        m = models.from_config(cfg, M=200)
+        states = random_states(m, 100, 1, seed=3, xs=[1.0], v_scale=0.0)
+        states[0].v[0] = f * 7e-4
+        upload(ens, states)
+        ens.timing(False)
+        ens.run(1)
+        counts[f] = ens.work()[0]
+        ens.close()
+    assert counts[0.0] <= 2 and 2 <= counts[1.0] <= 4 and counts[60.0] >= 8, counts
