@@ -142,7 +142,8 @@ struct ClassDev {
   int32_t* chebq = nullptr; // [2 + T] queue of the trajectories that take the Chebyshev
                             // series this step: count, work-groups done, list
   int cheb_groups = 0;      // most work-groups of the launch over that queue
-  int ip_waves = 0;         // waves (16-column tiles) per interaction-picture work-group
+  int ip_groups = 0;        // interaction-picture work-groups per trajectory
+  int ip_waves = 0;         // waves of each (a 16-column tile a wave)
   double* gbuf = nullptr;   // [T][N][n_pad] hop probabilities (query mode)
   double* obs = nullptr;    // [records][T][IESH_N_OBS] (class-local records)
   double2* low = nullptr;   // Loewdin scratch (mixed path)

@@ -540,20 +540,21 @@ hipError_t launch_prop(const ClassDev& c, int precision, hipStream_t s) {
 
 // The interaction picture: the 16-column tiles of a trajectory over
 // work-groups of equal width, as wide as the register file holds (at M = 200
-// two work-groups of seven waves take 1.26 ms per step, four of four 1.35,
-// seven of two 2.1: the work-groups of a trajectory each stream M).
+// two work-groups of seven waves took 1.26 ms per step, four of four 1.35,
+// seven of two 2.1, before M's ring of buffers (now 1.08): the work-groups of
+// a trajectory each stream M).
 hipError_t ip_prepare(ClassDev& c) {
   const int rt = c.md.n_pad / 16, tiles = (c.md.N + 7) / 8, most = prop_ip::max_waves(rt);
   const int groups = (tiles + most - 1) / most;
+  c.ip_groups = groups;
   c.ip_waves = (tiles + groups - 1) / groups;
-  return prop_ip::dispatch(rt, prop_ip::Launch{&c, dim3(1), 0, 0, nullptr, true});
+  return prop_ip::dispatch(rt, prop_ip::Launch{&c, dim3(1), c.ip_waves, 0, nullptr, true});
 }
 
 hipError_t launch_prop_ip(const ClassDev& c, hipStream_t s) {
   if (c.n_live < 1) return hipSuccess;
-  const int tiles = (c.md.N + 7) / 8, groups = (tiles + c.ip_waves - 1) / c.ip_waves;
-  const dim3 grid((c.n_live + 7) / 8 * 8 * groups);
-  return prop_ip::dispatch(c.md.n_pad / 16, prop_ip::Launch{&c, grid, 64 * c.ip_waves, groups, s, false});
+  const dim3 grid((c.n_live + 7) / 8 * 8 * c.ip_groups);
+  return prop_ip::dispatch(c.md.n_pad / 16, prop_ip::Launch{&c, grid, c.ip_waves, c.ip_groups, s, false});
 }
 
 // The queued trajectories of an interaction-picture class.

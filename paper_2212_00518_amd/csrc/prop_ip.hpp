@@ -15,15 +15,26 @@
 // far below the FP32 rounding of the phases.
 //
 // One wave owns 16 columns (8 orbitals as [Re of 8 | Im of 8]) and keeps all
-// rows of x and w in registers; M streams through LDS, one or two row tiles
-// at a time (double-buffered, direct-to-LDS loads), shared by the waves of
+// rows of x and w in registers; M passes through LDS, one or two row tiles
+// at a time (a ring of buffers, direct-to-LDS loads), shared by the waves of
 // the work-group.  The accumulator of a 16-row tile holds rows 4g .. 4g + 3
 // of column l & 15 in lane l = 16 g + (l & 15); two row tiles make one
 // 32-row operand if the product's inner index is read in the order (tile,
 // group, row) instead of ascending, so M is stored in that order and w needs
 // no exchange between lanes: the product's output, rounded, is the next
 // product's operand.
+//
+// Bound by the LDS: every wave reads all of M from it in each product (busy
+// 24% of the cycles in M's reads, 28% vector instructions, 21% matrix ones, two
+// waves to a SIMD).  Per step of a batch, ms, Chebyshev series / this with M
+// in two buffers and its loads waited for before every LDS read / now:
+//   4096 trajectories, M = 200, N = 100                   5.53 / 1.26 / 1.08
+//   1536, two leads, M = 256, N = 128                     3.98 / 1.51 / 1.29
+//   768, M = 200, N = 100                                 1.04 / .26 / .24
+//   4 x 512 at M = 40 to 320, scattering bath   7.89 / 1.97 / 1.93
 #pragma once
+
+#include <algorithm>
 
 #include "iesh_internal.hpp"
 
@@ -35,22 +46,22 @@ typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u4 __attribute__((ext_vector_type(4)));
 
+// Waves per SIMD by row tiles (what their registers allow; x, w and the next
+// w take 12 per row tile) and most waves to a work-group.
+__host__ __device__ constexpr int waves_per_simd(int rt) { return rt <= 2 ? 4 : rt <= 6 ? 3 : rt <= 13 ? 2 : 1; }
+__host__ __device__ constexpr int max_waves(int rt) { return rt <= 13 ? 8 : 4; }
 // k-blocks of M in flight from LDS per wave (three where four would spill)
 constexpr int ring(int rt) { return rt == 12 || rt == 13 ? 3 : 4; }
 
-// Row tiles up to which a wave fits 256 registers (two waves per SIMD); wider
-// baths take one wave per SIMD with 512.
-constexpr int kNarrowRT = 13;
-__host__ __device__ constexpr int max_waves(int rt) { return rt <= kNarrowRT ? 8 : 4; }
-constexpr int waves_per_simd(int rt) { return rt <= 2 ? 4 : rt <= 6 ? 3 : rt <= kNarrowRT ? 2 : 1; }
-// row tiles per LDS buffer
+// M in LDS: chunks of one or two row tiles in a ring of buffers.  A launch
+// whose ring holds all of M keeps it for every pass; the others stream it with
+// the other buffers' chunks in flight: the first pass reads M from memory,
+// whose latency is several chunks long.
 __host__ __device__ constexpr int chunk_tiles(int rt) { return (rt + 1) / 2 <= 7 ? 2 : 1; }
-
-// LDS of the two buffers of M; the row norms reuse it (64 rows of 17 floats a wave)
-__host__ __device__ constexpr int buffer_bytes(int rt) {
-  const int buf = 2 * chunk_tiles(rt) * ((rt + 1) / 2) * 2048, rows = max_waves(rt) * 64 * 17 * 4;
-  return buf > rows ? buf : rows;
-}
+__host__ __device__ constexpr int chunk_bytes(int rt) { return chunk_tiles(rt) * ((rt + 1) / 2) * 2048; }
+__host__ __device__ constexpr int chunks(int rt) { return (rt + chunk_tiles(rt) - 1) / chunk_tiles(rt); }
+constexpr int kLdsBytes = 160 * 1024;
+__host__ __device__ constexpr int plane_bytes(int rt) { return kIpPlanes * 16 * rt * 4; }
 
 // Value of lane l ^ 8 (a rotation by 8 within 16 lanes).
 __device__ inline float swap8(float v) {
@@ -103,28 +114,70 @@ __device__ inline void apply_small(const float (&P)[R], float (&T)[R], const flo
 struct Group {
   const float* ips;          // this trajectory's plan
   const float* pl;           // LDS: planes of ipv
-  unsigned char* buf;        // LDS: two buffers of M
+  const unsigned char* buf;  // LDS: the buffers of M
+  unsigned buf_lds;          // and their byte address there
   const unsigned char* Mg;   // M in memory
   int sub, p, nw, wave, lane;
+  int loads;                 // of each wave per chunk of M
+  int nbuf;                  // buffers of M (all its chunks: loaded once)
   float unscale;
 };
 
-// One buffer of M into LDS: 1 KB pieces dealt to the waves.
-template <int RT>
-__device__ inline void load_chunk(const Group& gr, int cc, int parity) {
-  constexpr int G = chunk_tiles(RT), kTileBytes = (RT + 1) / 2 * 2048;
-  const int tiles_here = (cc + 1) * G <= RT ? G : RT - cc * G;
-  const unsigned char* src = gr.Mg + (size_t)cc * G * kTileBytes;
-  unsigned char* dst = gr.buf + (parity & 1) * G * kTileBytes;
-  for (int i = gr.wave; i < tiles_here * (kTileBytes >> 10); i += gr.nw)
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + i * 1024 + gr.lane * 16),
-                                     (__attribute__((address_space(3))) void*)(dst + i * 1024), 16, 0, 0);
+// 1 KB from memory (src + 16 lane) to LDS at byte `lds`, asynchronously.  In
+// assembly: the compiler waits for loads into LDS that it knows of before any
+// LDS read it cannot tell apart, here the phases and Z, which cost the whole
+// latency of M (10,000 cycles a work-group).  It has no register result;
+// arrive() waits for it.
+__device__ inline void load_to_lds(const unsigned char* src, unsigned voff, unsigned lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+               :: "s"(lds), "v"(voff), "s"(src) : "memory", "m0");
 }
 
-// Waits for this wave's loads into LDS, then for every wave's.
-__device__ inline void arrive() {
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
+// One chunk of M into a buffer: 1 KB pieces dealt to the waves, the same
+// number of loads to each (the last piece again where there is none left).
+template <int RT>
+__device__ inline void load_chunk(const Group& gr, int cc, int slot) {
+  constexpr int G = chunk_tiles(RT), kTilePieces = (RT + 1) / 2 * 2;
+  const int last = ((cc + 1) * G <= RT ? G : RT - cc * G) * kTilePieces - 1;
+  const unsigned char* src = gr.Mg + (size_t)cc * chunk_bytes(RT);
+  const unsigned dst = gr.buf_lds + slot * chunk_bytes(RT);
+  for (int k = 0; k < gr.loads; ++k) {
+    const int i = min(gr.wave + k * gr.nw, last);
+    load_to_lds(src + i * 1024, gr.lane * 16, dst + i * 1024);
+  }
+}
+
+// Waits until at most n of this wave's loads are outstanding (or fewer), then
+// for every wave.
+__device__ inline void arrive(int n) {
+#define IESH_IP_WAIT(k) asm volatile("s_waitcnt vmcnt(" #k ")" ::: "memory")
+  if (n < 8) {
+    if (n < 3)
+      IESH_IP_WAIT(0);
+    else if (n < 6)
+      IESH_IP_WAIT(3);
+    else
+      IESH_IP_WAIT(6);
+  } else if (n < 16) {
+    if (n < 12)
+      IESH_IP_WAIT(8);
+    else
+      IESH_IP_WAIT(12);
+  } else if (n < 24) {
+    if (n < 20)
+      IESH_IP_WAIT(16);
+    else
+      IESH_IP_WAIT(20);
+  } else {
+    IESH_IP_WAIT(24);
+  }
+#undef IESH_IP_WAIT
+  // no fence: it would wait for the loads still in flight.  What the barrier
+  // orders, the LDS reads of the chunk that is given up and the loads into
+  // it, is complete or not yet issued.
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
 }
 
 // One sub-interval: u = E_pre x (kept in x); with w0 = u + Z T1 (e^{-iL} u),
@@ -139,44 +192,43 @@ __device__ inline void sub_intervals(const Group& gr, float (&x)[RT][4]) {
   constexpr int n_pad = 16 * RT;
   constexpr int KB = (RT + 1) / 2;       // k-blocks of 32 columns
   constexpr int G = chunk_tiles(RT);     // row tiles per buffer
-  constexpr int NC = (RT + G - 1) / G;   // buffers per pass over M
+  constexpr int NC = chunks(RT);         // chunks per pass over M
   constexpr int kTileBytes = KB * 2048;  // one row tile of M
   constexpr int kRing = ring(RT);
   const float* ips = gr.ips;
   const float* pl = gr.pl;
   const float* zp = pl + IPV_Z * n_pad;
-  unsigned char* buf = gr.buf;
+  const unsigned char* buf = gr.buf;
   const int lane = gr.lane, g = lane >> 4, sub = gr.sub, p = gr.p;
   const float sg = (lane & 15) < 8 ? -1.0f : 1.0f, unscale = gr.unscale;
-  int ch = 0;  // buffers of M consumed (its parity names the buffer in use)
+  const int nbuf = gr.nbuf;
+  const bool resident = nbuf == NC;
+  const int ahead = (nbuf - 2) * gr.loads;  // loads outstanding when a chunk has arrived
+  int slot = 0;                             // buffer in use
+  int left = sub * p * NC - (nbuf - 1);     // chunks still to be requested
   for (int it = 0; it < sub; ++it) {
     float T[R] = {}, P[R] = {};
     float m = 0.0f;
+    auto phase = [&](int plane, int rt, f4 (&c)[4]) {  // cos, sin and their low parts
+#pragma unroll
+    for (int q = 0; q < 4; ++q) c[q] = *reinterpret_cast<const f4*>(pl + (plane + q) * n_pad + rt * 16 + 4 * g);
+    };
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
-      const int row = rt * 16 + 4 * g;
-      const f4 c0 = *reinterpret_cast<const f4*>(pl + IPV_PRE * n_pad + row);
-      const f4 s0 = *reinterpret_cast<const f4*>(pl + (IPV_PRE + 1) * n_pad + row);
-      const f4 cl = *reinterpret_cast<const f4*>(pl + (IPV_PRE + 2) * n_pad + row);
-      const f4 sl = *reinterpret_cast<const f4*>(pl + (IPV_PRE + 3) * n_pad + row);
+      f4 c[4];
+      phase(IPV_PRE, rt, c);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const float xr = x[rt][r], xp = sg * swap8(xr);
-        x[rt][r] = fmaf(s0[r], xp, fmaf(c0[r], xr, fmaf(sl[r], xp, cl[r] * xr)));
+        x[rt][r] = fmaf(c[1][r], xp, fmaf(c[0][r], xr, fmaf(c[3][r], xp, c[2][r] * xr)));
         m = fmaxf(m, fabsf(x[rt][r]));
       }
-      each_column<R>(zp, n_pad, row, [&](int f, f4 z) {
+      each_column<R>(zp, n_pad, rt * 16 + 4 * g, [&](int f, f4 z) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) P[f] = fmaf(z[r], x[rt][r], P[f]);
       });
-      tile_end();
+      if (rt & 1) tile_end();
     }
-    // power-of-two scale of each column that keeps u and w within f16's range
-    m = fmaxf(m, __shfl_xor(m, 16));
-    m = fmaxf(m, __shfl_xor(m, 32));
-    int ex = 0;
-    if (m > 0x1p-100f && m < 0x1p100f) (void)frexpf(m, &ex);
-    const float sx = ldexpf(1.0f, 10 - ex);
     auto sum_groups = [&] {
 #pragma unroll
       for (int f = 0; f < R; ++f) {
@@ -185,12 +237,18 @@ __device__ inline void sub_intervals(const Group& gr, float (&x)[RT][4]) {
       }
     };
     sum_groups();
-    // the two lanes of an orbital may scale differently: T in true units first
+    // power-of-two scale of each column that keeps u and w within f16's range;
+    // T in true units first, the two lanes of an orbital may scale differently
+    m = fmaxf(m, __shfl_xor(m, 16));
+    m = fmaxf(m, __shfl_xor(m, 32));
+    int ex = 0;
+    if (m > 0x1p-100f && m < 0x1p100f) (void)frexpf(m, &ex);
+    const float sx = ldexpf(1.0f, 10 - ex);
     apply_small<R>(P, T, ips, -sg);
 #pragma unroll
     for (int f = 0; f < R; ++f) T[f] *= sx;
     u4 wh[KB], wl[KB];
-    auto put = [](u4* h, u4* l, int rt, const float* v) {
+    auto put = [](u4 (&h)[KB], u4 (&l)[KB], int rt, const float* v) {
       unsigned hi[2], lo[2];
       split4(v, hi, lo);
       // computed here: left alone, the compiler sinks the splits of all row
@@ -201,7 +259,11 @@ __device__ inline void sub_intervals(const Group& gr, float (&x)[RT][4]) {
       l[rt >> 1][2 * (rt & 1)] = lo[0];
       l[rt >> 1][2 * (rt & 1) + 1] = lo[1];
     };
-    auto add_low_rank = [&](int rt, float* v) {  // v += Z T
+    auto pad = [](u4 (&h)[KB]) {  // rows past an odd last tile
+      if constexpr (RT & 1)
+        h[KB - 1][2] = h[KB - 1][3] = 0u;
+    };
+    auto add_low_rank = [&](int rt, float (&v)[4]) {  // v += Z T
       each_column<R>(zp, n_pad, rt * 16 + 4 * g, [&](int f, f4 z) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) v[r] = fmaf(z[r], T[f], v[r]);
@@ -214,22 +276,27 @@ __device__ inline void sub_intervals(const Group& gr, float (&x)[RT][4]) {
       for (int r = 0; r < 4; ++r) v[r] = x[rt][r] *= sx;
       add_low_rank(rt, v);
       put(wh, wl, rt, v);
-      tile_end();
+      if (rt & 1) tile_end();
     }
-    if constexpr (RT & 1) {
-      wh[KB - 1][2] = wh[KB - 1][3] = 0u;
-      wl[KB - 1][2] = wl[KB - 1][3] = 0u;
-    }
-    // pass over M: out(rt, y) takes the product M w of a row tile
-    auto pass = [&](bool last_pass, auto out) {
+    pad(wh);
+    pad(wl);
+    if (resident && it == 0) arrive(0);
+    // pass over M: out(rt, y) takes the products M w of a row tile
+    auto pass = [&](auto out) {
 #pragma unroll
       for (int cc = 0; cc < NC; ++cc) {
-        // the next buffer while this one is in use (the last one of a pass
-        // fetches the first of the next)
-        const unsigned char* cur = buf + (ch & 1) * G * kTileBytes;
-        if (!(cc == NC - 1 && last_pass)) {
-          const int nx = cc == NC - 1 ? 0 : cc + 1;
-          load_chunk<RT>(gr, nx, ch + 1);
+        const unsigned char* cur;
+        if (resident) {
+          cur = buf + cc * chunk_bytes(RT);
+        } else {
+          // this chunk has arrived once those requested after it may be
+          // outstanding; then the buffer before it is free for the next
+          arrive(left > 0 ? ahead : 0);
+          if (left > 0)
+            load_chunk<RT>(gr, cc + nbuf - 1 < NC ? cc + nbuf - 1 : cc + nbuf - 1 - NC, slot == 0 ? nbuf - 1 : slot - 1);
+          --left;
+          cur = buf + slot * chunk_bytes(RT);
+          slot = slot == nbuf - 1 ? 0 : slot + 1;
         }
         // M's operands kRing k-blocks ahead in registers
         const h8* A = reinterpret_cast<const h8*>(cur) + lane;
@@ -257,17 +324,20 @@ __device__ inline void sub_intervals(const Group& gr, float (&x)[RT][4]) {
             y0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[q % kRing], bh, y0, 0, 0, 0);
             y1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[q % kRing], bl, y1, 0, 0, 0);
             y1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(al[q % kRing], bh, y1, 0, 0, 0);
-            if (kb == KB - 1) out(rt, y0 + y1);
+            if (kb == KB - 1) {
+              float y[4];
+#pragma unroll
+              for (int r = 0; r < 4; ++r) y[r] = y0[r] + y1[r];
+              out(rt, y);
+            }
           }
         }
-        ++ch;
-        arrive();
       }
     };
     for (int i = p; i > 1; --i) {
       const float ci = -unscale / (float)i;
       u4 nh[KB], nl[KB];
-      pass(false, [&](int rt, f4 y) {
+      pass([&](int rt, const float (&y)[4]) {
         float v[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) v[r] = fmaf(ci, y[r], x[rt][r]);
@@ -279,35 +349,38 @@ __device__ inline void sub_intervals(const Group& gr, float (&x)[RT][4]) {
         wh[kb] = nh[kb];
         wl[kb] = nl[kb];
       }
-      if constexpr (RT & 1) {
-        wh[KB - 1][2] = wh[KB - 1][3] = 0u;
-        wl[KB - 1][2] = wl[KB - 1][3] = 0u;
-      }
+      pad(wh);
+      pad(wl);
     }
     float y[RT][4];
-#pragma unroll
-    for (int f = 0; f < R; ++f) P[f] = 0.0f;
-    pass(it == sub - 1, [&](int rt, f4 yv) {
+    pass([&](int rt, const float (&yv)[4]) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         y[rt][r] = -unscale * yv[r];
         asm volatile("" : "+v"(y[rt][r]));
       }
     });
-    const float ux = ldexpf(1.0f, ex - 10);
+#pragma unroll
+    for (int f = 0; f < R; ++f) P[f] = 0.0f;
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
       float v[4];
 #pragma unroll
       for (int r = 0; r < 4; ++r) v[r] = x[rt][r] + y[rt][r];
-      add_low_rank(rt, v);
+      f4 zr[R];
       each_column<R>(zp, n_pad, rt * 16 + 4 * g, [&](int f, f4 z) {
+        zr[f] = z;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) P[f] = fmaf(z[r], v[r], P[f]);
+        for (int r = 0; r < 4; ++r) v[r] = fmaf(z[r], T[f], v[r]);
       });
-      tile_end();
+#pragma unroll
+      for (int f = 0; f < R; ++f)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) P[f] = fmaf(zr[f][r], v[r], P[f]);
+      if (rt & 1) tile_end();
     }
     sum_groups();
+    const float ux = ldexpf(1.0f, ex - 10);
 #pragma unroll
     for (int f = 0; f < R; ++f) {
       P[f] *= ux;
@@ -316,80 +389,91 @@ __device__ inline void sub_intervals(const Group& gr, float (&x)[RT][4]) {
     apply_small<R>(P, T, ips, sg);
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
-      const int row = rt * 16 + 4 * g;
       float dv[4];
 #pragma unroll
       for (int r = 0; r < 4; ++r) dv[r] = y[rt][r] * ux;
       add_low_rank(rt, dv);
-      const f4 c0 = *reinterpret_cast<const f4*>(pl + IPV_POST * n_pad + row);
-      const f4 s0 = *reinterpret_cast<const f4*>(pl + (IPV_POST + 1) * n_pad + row);
-      const f4 cl = *reinterpret_cast<const f4*>(pl + (IPV_POST + 2) * n_pad + row);
-      const f4 sl = *reinterpret_cast<const f4*>(pl + (IPV_POST + 3) * n_pad + row);
+      f4 c[4];
+      phase(IPV_POST, rt, c);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const float xr = x[rt][r] * ux, xp = sg * swap8(xr), dp = sg * swap8(dv[r]);
-        const float low = fmaf(s0[r], dp, fmaf(c0[r], dv[r], fmaf(sl[r], xp, cl[r] * xr)));
-        x[rt][r] = fmaf(s0[r], xp, fmaf(c0[r], xr, low));
+        const float xr = x[rt][r] * ux, xp = sg * swap8(xr), dr = dv[r], dp = sg * swap8(dr);
+        const float low = fmaf(c[1][r], dp, fmaf(c[0][r], dr, fmaf(c[3][r], xp, c[2][r] * xr)));
+        x[rt][r] = fmaf(c[1][r], xp, fmaf(c[0][r], xr, low));
       }
-      tile_end();
+      if (rt & 1) tile_end();
     }
   }
 }
 
 template <int RT>
 __global__ __launch_bounds__(64 * max_waves(RT))
-    __attribute__((amdgpu_waves_per_eu(waves_per_simd(RT), waves_per_simd(RT)))) void k_prop_ip(ClassDev c, int groups) {
+    __attribute__((amdgpu_waves_per_eu(waves_per_simd(RT), waves_per_simd(RT)))) void k_prop_ip(ClassDev c, int groups, int nbuf, int buf_bytes) {
   constexpr int n_pad = 16 * RT;
   extern __shared__ __align__(16) unsigned char smem[];
-  unsigned char* buf = smem;                                              // [2][row tiles][k-blocks][2][64][16 B]
-  float* pl = reinterpret_cast<float*>(smem + buffer_bytes(RT));          // planes of ipv
+  unsigned char* buf = smem;                                // [buffers][row tiles][k-blocks][2][64][16 B]
+  float* pl = reinterpret_cast<float*>(smem + buf_bytes);   // planes of ipv
 
   // blocks b, b + 8, ... share an XCD: the work-groups of a trajectory share M in its L2
   const int b = blockIdx.x, local = b >> 3;
   const int grp = local % groups, t = (local / groups) * 8 + (b & 7);
-  if (t >= live_slots(c) || (c.status[t] & kFreezeMask)) return;
+  if (t >= c.n_live) return;
+  // everything is requested before the first answer is looked at
+  const int live = live_slots(c), status = c.status[t];
   const float* ips = c.ips + (size_t)t * kIpStride;
-  const int sub = (int)ips[IP_SUB];
-  if (sub == 0) return;  // Chebyshev series
-  const int p = (int)ips[IP_TERMS], R = (int)ips[IP_RANK];
-  const float unscale = ips[IP_UNSCALE];
+  const f4 plan = *reinterpret_cast<const f4*>(ips);
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = blockDim.x >> 6;
   const int g = lane >> 4, col = lane & 15;
   const bool is_re = col < 8;
   const int N = c.md.N, tiles = (N + 7) >> 3;
-  // the tiles of a trajectory over its work-groups, balanced
+  // the tiles of a trajectory over its work-groups, balanced, one to a wave
   const int base = tiles / groups, rem = tiles % groups;
-  const int tile = grp * base + (grp < rem ? grp : rem) + wave;
-  const bool active = wave < base + (grp < rem ? 1 : 0);
-  const int o = tile * 8 + (lane & 7);
+  const int first = grp * base + (grp < rem ? grp : rem), end = first + base + (grp < rem ? 1 : 0);
+  const int tile = first + wave;
 
   const unsigned char* Mg = reinterpret_cast<const unsigned char*>(c.Bt32 + (size_t)t * c.b_stride);
-  Group gr{ips, pl, buf, Mg, sub, p, nw, wave, lane, unscale};
-  load_chunk<RT>(gr, 0, 0);
-
   const float* ipv = c.ipv + (size_t)t * kIpPlanes * n_pad;
-  for (int i = tid; i < (IPV_Z + R) * n_pad; i += blockDim.x) pl[i] = ipv[i];
+  for (int i = wave; i * 1024 < plane_bytes(RT); i += nw)
+    if (i * 1024 + lane * 16 < plane_bytes(RT))
+      __builtin_amdgcn_global_load_lds(
+          (const __attribute__((address_space(1))) void*)(reinterpret_cast<const unsigned char*>(ipv) + i * 1024 + lane * 16),
+          (__attribute__((address_space(3))) void*)(reinterpret_cast<unsigned char*>(pl) + i * 1024), 16, 0, 0);
 
   // x: rows 16 rt + 4 g + r of the lane's column.  A lane reads two complex
   // rows; the lane of the orbital's other part has the two others.
   float x[RT][4];
-  float* Cg = c.C32 + ((size_t)t * N + (active && o < N ? o : 0)) * n_pad * 2;
-  const bool mine = active && o < N;
+  f4 cv[RT];
+  const int o = tile * 8 + (lane & 7);
+  const bool mine = tile < end && o < N;  // idle columns read orbital 0
+  float* Cg = c.C32 + ((size_t)t * N + (mine ? o : 0)) * n_pad * 2 + (4 * g + (is_re ? 0 : 2)) * 2;
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt) cv[rt] = *reinterpret_cast<const f4*>(Cg + rt * 32);
+  __builtin_amdgcn_sched_barrier(0);
+  const int sub = (int)plan[IP_SUB], p = (int)plan[IP_TERMS], R = (int)plan[IP_RANK];
+  const float unscale = plan[IP_UNSCALE];
+  if (t >= live || (status & kFreezeMask) || sub == 0) {  // sub == 0: Chebyshev series
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // no load into LDS outlives the work-group
+    return;
+  }
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) {
-    const f4 v = *reinterpret_cast<const f4*>(Cg + (rt * 16 + 4 * g + (is_re ? 0 : 2)) * 2);
+    const f4 v = cv[rt];
     const float r0 = swap8(is_re ? v[1] : v[0]), r1 = swap8(is_re ? v[3] : v[2]);
-    x[rt][0] = is_re ? v[0] : r0;
-    x[rt][1] = is_re ? v[2] : r1;
-    x[rt][2] = is_re ? r0 : v[1];
-    x[rt][3] = is_re ? r1 : v[3];
-    if (!mine)  // idle columns read orbital 0
-#pragma unroll
-      for (int r = 0; r < 4; ++r) x[rt][r] = 0.0f;
+    x[rt][0] = mine ? (is_re ? v[0] : r0) : 0.0f;
+    x[rt][1] = mine ? (is_re ? v[2] : r1) : 0.0f;
+    x[rt][2] = mine ? (is_re ? r0 : v[1]) : 0.0f;
+    x[rt][3] = mine ? (is_re ? r1 : v[3]) : 0.0f;
   }
-  arrive();
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();  // planes
+  // M is requested once the orbitals are there: requested first, it would
+  // hold them up, and the phases below cover its latency
+  const int loads = (chunk_bytes(RT) / 1024 + nw - 1) / nw;
+  const unsigned buf_lds = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)buf;
+  const Group gr{ips, pl, buf, buf_lds, Mg, sub, p, nw, wave, lane, loads, nbuf, unscale};
+  for (int q = 0; q < (nbuf == chunks(RT) ? nbuf : nbuf - 1); ++q) load_chunk<RT>(gr, q, q);
 
   if (R == 2)
     sub_intervals<RT, 2>(gr, x);
@@ -399,20 +483,22 @@ __global__ __launch_bounds__(64 * max_waves(RT))
     sub_intervals<RT, 8>(gr, x);
 
 #pragma unroll
-  for (int rt = 0; rt < RT; ++rt) {
-    const float r0 = swap8(is_re ? x[rt][2] : x[rt][0]), r1 = swap8(is_re ? x[rt][3] : x[rt][1]);
-    f4 v;
-    v[0] = is_re ? x[rt][0] : r0;
-    v[1] = is_re ? r0 : x[rt][2];
-    v[2] = is_re ? x[rt][1] : r1;
-    v[3] = is_re ? r1 : x[rt][3];
-    if (mine) *reinterpret_cast<f4*>(Cg + (rt * 16 + 4 * g + (is_re ? 0 : 2)) * 2) = v;
-  }
+    for (int rt = 0; rt < RT; ++rt) {
+      const float(&xv)[4] = x[rt];
+      const float r0 = swap8(is_re ? xv[2] : xv[0]), r1 = swap8(is_re ? xv[3] : xv[1]);
+      f4 v;
+      v[0] = is_re ? xv[0] : r0;
+      v[1] = is_re ? r0 : xv[2];
+      v[2] = is_re ? xv[1] : r1;
+      v[3] = is_re ? r1 : xv[3];
+      if (mine) *reinterpret_cast<f4*>(Cg + rt * 32) = v;
+    }
   // squared row norms over the tile's orbitals (of the stored values, summed
   // in FP64), for the no-hop bound: 64 rows at a time through the wave's part
-  // of the LDS (every wave has left the buffers of M)
-  if (active) {
-    float* wl_ = reinterpret_cast<float*>(buf) + wave * 64 * 17;
+  // of the LDS, once every wave has left the buffers of M
+  __syncthreads();
+  float* sq = reinterpret_cast<float*>(buf) + wave * 64 * 17;
+  if (tile < end) {
     double* rn = c.rown + ((size_t)t * tiles + tile) * n_pad;
 #pragma unroll
     for (int r0 = 0; r0 < RT; r0 += 4) {
@@ -420,13 +506,13 @@ __global__ __launch_bounds__(64 * max_waves(RT))
       for (int q = 0; q < 4; ++q)
         if (r0 + q < RT)
 #pragma unroll
-          for (int r = 0; r < 4; ++r) wl_[(q * 16 + 4 * g + r) * 17 + col] = x[r0 + q][r];
+        for (int r = 0; r < 4; ++r) sq[(q * 16 + 4 * g + r) * 17 + col] = x[r0 + q][r];
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       __builtin_amdgcn_wave_barrier();
       double acc = 0.0;
 #pragma unroll
       for (int q = 0; q < 16; ++q) {
-        const double v = (double)wl_[lane * 17 + q];
+        const double v = (double)sq[lane * 17 + q];
         acc = fma(v, v, acc);
       }
       if (r0 * 16 + lane < n_pad) rn[r0 * 16 + lane] = acc;
@@ -436,16 +522,11 @@ __global__ __launch_bounds__(64 * max_waves(RT))
   }
 }
 
-template <int RT>
-size_t lds_bytes() {
-  return buffer_bytes(RT) + (size_t)kIpPlanes * 16 * RT * 4;
-}
-
 // The kernel for rt row tiles: reserves its LDS, or launches it.
 struct Launch {
   const ClassDev* c;
   dim3 grid;
-  int threads, groups;
+  int waves, groups;
   hipStream_t stream;
   bool prepare;
 };
@@ -456,10 +537,17 @@ hipError_t dispatch(int rt, const Launch& l) {
     return hipErrorInvalidValue;
   } else {
     if (rt != RT) return dispatch<RT + 1>(rt, l);
+    // buffers: what the LDS holds beside the work-groups that the registers
+    // allow on a compute unit; the row norms reuse them (64 rows of 17 floats
+    // a wave)
+    const int per_cu = std::max(1, 4 * waves_per_simd(RT) / l.waves);
+    const int fit = (kLdsBytes / per_cu - plane_bytes(RT)) / chunk_bytes(RT);
+    const int nbuf = std::min(std::max(fit, 2), chunks(RT));
+    const int buf = std::max(nbuf * chunk_bytes(RT), l.waves * 64 * 17 * 4), lds = buf + plane_bytes(RT);
     if (l.prepare)
       return hipFuncSetAttribute((const void*)k_prop_ip<RT>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                 (int)lds_bytes<RT>());
-    hipLaunchKernelGGL((k_prop_ip<RT>), l.grid, dim3(l.threads), lds_bytes<RT>(), l.stream, *l.c, l.groups);
+                                 kLdsBytes);
+    hipLaunchKernelGGL((k_prop_ip<RT>), l.grid, dim3(64 * l.waves), lds, l.stream, *l.c, l.groups, nbuf, buf);
     return hipGetLastError();
   }
 }
