@@ -484,9 +484,10 @@ int iesh_sync(iesh_ctx* ctx);
    (1 <= n <= IESH_JACOBI_MAX_N): the fallback for a one-electron Hamiltonian
    that is not an arrowhead (Eq. single_electron_discrete_electronic_hamiltonian
    for H of any structure).  Cyclic two-sided Jacobi rotations, FP64, one
-   work-group per matrix with the matrix in LDS up to IESH_JACOBI_LDS_N, in a
-   device workspace beyond (2 m (m + 1) doubles per matrix, m = n rounded up to
-   even; the call allocates it, waits for the kernel and frees it).
+   work-group per matrix with everything in LDS up to IESH_JACOBI_LDS_N; beyond,
+   two kernels per sweep with a device workspace (2 m (m + 1) doubles per
+   matrix, m = n rounded up to even; the call allocates it, waits for the
+   kernels and frees it) and Q as scratch until the vectors are written.
      H      : batch x n x n row-major (only symmetric input is meaningful)
      lam    : batch x n eigenvalues, ascending
      Q      : batch x n x n row-major, column j = eigenvector of lam[j]; the
@@ -512,7 +513,7 @@ int iesh_eigh_batched(const double* H, int32_t n, int32_t batch, double* lam, do
      H, lam, Q, sweeps : device pointers on the current device, layouts as in
                          iesh_eigh_batched (sweeps may be NULL)
      hip_stream        : hipStream_t (NULL = the null stream); the call only
-                         enqueues the kernel and does not synchronise.
+                         enqueues the kernels and does not synchronise.
    Argument errors return IESH_EINVAL, launch errors IESH_EDEVICE;
    iesh_last_error(NULL) gives the reason. */
 int iesh_eigh_batched_noalloc(const double* H, int32_t n, int32_t batch, double* lam, double* Q,

@@ -10,7 +10,7 @@
 // device current, and kept in g_scratch_ptr.  Every call on a device shares
 // that device's array, so calls that overlap on one GPU (different streams,
 // or different host threads) race; calls on one stream are ordered by it.
-// The Jacobi kernel initialises every work-space element it reads (the
+// The Jacobi kernels initialise every work-space element they read (the
 // matrix from H, the rotations from the identity), so nothing needs to be
 // cleared between calls.
 

@@ -1,0 +1,59 @@
+"""The split eigen-solver of orders beyond the LDS-resident one: even and odd
+half orders, one to three pairs to a lane, the triangle in LDS and in memory,
+matrices that converge in different sweeps, and the eigenvectors written over
+the matrices.
+
+Tolerances as for the solver at every order (FP64): eigenvalues 1e-13 of the
+spectral norm, residual and orthogonality 1e-13 sqrt(n).
+"""
+import ctypes
+
+import numpy as np
+import pytest
+
+from test_gpu_eigh import _check_decomposition, gpu  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+def _matrices(n, batch):
+    rs = np.random.default_rng(n)
+    A = rs.normal(size=(batch, n, n))
+    H = 0.5 * (A + np.transpose(A, (0, 2, 1)))
+    H[0] = np.diag(np.arange(n)[::-1] * 1.0)  # converged at once
+    H[1] = np.diag(np.full(n, 0.3)) + 1e-6 * H[1]
+    H[2, :, :] = np.kron(np.eye((n + 2) // 3), [[0.0, 1, 1], [1, 0, 1], [1, 1, 0]])[:n, :n]  # repeated eigenvalues
+    return H
+
+
+# pairs of a round 49, 50, 64, 65, 100, 101 (the last triangle in LDS), 101 and
+# 102 (the first in memory), 128, 129, 168
+@pytest.mark.parametrize("n", [97, 99, 100, 127, 128, 129, 200, 201, 202, 203, 256, 257, 335, 336])
+def test_orders_around_the_splits(n):
+    from paper_2212_00518_amd import eigh_batched
+    H = _matrices(n, 5)
+    lam, Q, sw = eigh_batched(H)
+    assert sw[0] == 1 and np.all(sw > 0) and np.all(sw[1:] > 1), sw
+    for b in range(len(H)):
+        _check_decomposition(H[b], lam[b], Q[b])
+
+
+@pytest.mark.parametrize("entry", ["iesh_eigh_batched", "iesh_eigh_batched_noalloc"])
+@pytest.mark.parametrize("n", [101, 201, 230])
+def test_vectors_over_the_matrices(n, entry):
+    import torch
+    from paper_2212_00518_amd import _lib, eigh_batched
+    H = _matrices(n, 4)
+    lam_h, Q_h, sw_h = eigh_batched(H)
+    buf = torch.from_numpy(H).cuda()
+    lam = torch.zeros((4, n), dtype=torch.float64, device="cuda")
+    sw = torch.zeros(4, dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    args = [ctypes.c_void_p(buf.data_ptr()), n, 4, ctypes.c_void_p(lam.data_ptr()), ctypes.c_void_p(buf.data_ptr()),
+            ctypes.c_void_p(sw.data_ptr())]
+    args += [None] if entry.endswith("noalloc") else [_lib.IESH_MEM_DEVICE, None]
+    assert getattr(_lib.lib(), entry)(*args) == _lib.IESH_OK
+    torch.cuda.synchronize()
+    assert np.array_equal(lam.cpu().numpy(), lam_h)
+    assert np.array_equal(buf.cpu().numpy(), Q_h)
+    assert np.array_equal(sw.cpu().numpy(), sw_h)
