@@ -546,13 +546,10 @@ int enqueue_compact(iesh_ctx* ctx) {
   return IESH_OK;
 }
 
+// The device's step counter lies one behind between steps (a step's first
+// launch moves it on).
 int set_counters(iesh_ctx* ctx, int64_t run_step0, int64_t record_every) {
-  // step, run_step0 are the first two fields; record_every the fourth
-  const int64_t head[2] = {ctx->step, run_step0};
-  HIPTRY(ctx, hipMemcpyAsync(ctx->cnt, head, sizeof(head), hipMemcpyHostToDevice, ctx->stream));
-  HIPTRY(ctx, hipMemcpyAsync(&ctx->cnt->record_every, &record_every, sizeof(int64_t),
-                             hipMemcpyHostToDevice, ctx->stream));
-  HIPTRY(ctx, hipStreamSynchronize(ctx->stream));
+  HIPTRY(ctx, launch_set_counters(ctx->cnt, ctx->step - 1, run_step0, record_every, ctx->stream));
   return IESH_OK;
 }
 
@@ -595,13 +592,21 @@ int enqueue_step(iesh_ctx* ctx, int record) {
   Counters* cnt = ctx->cnt;
   const int S = r.elec_substeps;
   const std::vector<ClassSet> arrow = class_sets(ctx, false), dense = class_sets(ctx, true);
+  bool advance = true;  // of the next launch that has blocks
   auto eig = [&](int sub, int nsub) -> int {
-    for (const ClassSet& set : arrow)
+    for (const ClassSet& set : arrow) {
       HIPTRY(ctx, timed(ctx, IESH_TIMER_EIG,
-                        [&] { return launch_eig_fused(set, r.dt, r.precision, cnt, s, sub, nsub); }));
+                        [&] { return launch_eig_fused(set, r.dt, r.precision, cnt, s, sub, nsub, advance); }));
+      if (set.n > 0 && set.first[set.n] > 0) advance = false;
+    }
     for (auto& c : ctx->cls)
-      if (c.n_traj && c.Gd)
-        HIPTRY(ctx, timed(ctx, IESH_TIMER_EIG, [&] { return launch_dense_step(c, r.dt, cnt, s, sub, nsub); }));
+      if (c.n_traj && c.Gd) {
+        HIPTRY(ctx, timed(ctx, IESH_TIMER_EIG,
+                          [&] { return launch_dense_step(c, r.dt, cnt, s, sub, nsub, advance); }));
+        if (c.n_live > 0) advance = false;
+      }
+    if (advance) HIPTRY(ctx, launch_advance(cnt, s));
+    advance = false;
     return IESH_OK;
   };
   auto prop = [&]() -> int {
@@ -639,7 +644,6 @@ int enqueue_step(iesh_ctx* ctx, int record) {
       HIPTRY(ctx, timed(ctx, IESH_TIMER_LOWDIN,
                         [&] { return launch_lowdin(c, cnt, r.lowdin_every, c.low, s); }));
   }
-  HIPTRY(ctx, launch_advance(ctx->cnt, ctx->stream));
   return IESH_OK;
 }
 
@@ -1069,7 +1073,7 @@ int iesh_create(const iesh_model_desc* models, int32_t n_models, const int32_t* 
   // are resident at once
   for (auto& c : ctx->cls)
     if (c.n_traj) c.hop_groups = hop_resident_groups(c, r.precision, ctx->n_cu);
-  if (set_counters(ctx, 0, 0)) return bail(IESH_EDEVICE);
+  if (set_counters(ctx, 0, 0) || hipStreamSynchronize(ctx->stream) != hipSuccess) return bail(IESH_EDEVICE);
   if (reset_perm(ctx)) return bail(IESH_EDEVICE);
   *out = ctx;
   return IESH_OK;
@@ -1123,7 +1127,10 @@ int iesh_query_sizes(const iesh_ctx* ctx, iesh_sizes* out) {
 int iesh_set_step(iesh_ctx* ctx, int64_t step) {
   if (!ctx || step < 0) return IESH_EINVAL;
   ctx->step = step;
-  return set_counters(ctx, step, 0);
+  const int rc = set_counters(ctx, step, 0);
+  if (rc) return rc;
+  HIPTRY(ctx, hipStreamSynchronize(ctx->stream));
+  return IESH_OK;
 }
 
 int iesh_get_step(const iesh_ctx* ctx, int64_t* step) {

@@ -176,7 +176,7 @@ struct ClassDev {
 };
 
 struct Counters {
-  int64_t step;          // global step counter (hop uniform counter)
+  int64_t step;          // global step counter (hop uniform counter); the last step's between steps
   int64_t run_step0;     // first step of the current iesh_run call
   int64_t n_events;      // events recorded
   int64_t record_every;
@@ -353,7 +353,7 @@ hipError_t launch_eig_step(const ClassDev& c, double dt, Counters* cnt, hipStrea
 hipError_t launch_eig_query(const ClassDev& c, int t0, int nt, hipStream_t s);
 // the step of several arrowhead classes in one launch
 hipError_t launch_eig_fused(const ClassSet& set, double dt, int precision, Counters* cnt, hipStream_t s,
-                            int sub = -1, int nsub = 1);
+                            int sub = -1, int nsub = 1, bool advance = false);
 hipError_t launch_init_thermal(const ClassDev& c, double kT, double bias, uint64_t seed,
                                hipStream_t s);
 // dense symmetric eigen-decomposition (k_jacobi.hip)
@@ -364,7 +364,7 @@ hipError_t launch_forces(const ClassDev& c, hipStream_t s);
 // dense model kind (k_dense.hip)
 size_t dense_lds_size(int n_pad);
 hipError_t launch_dense_step(const ClassDev& c, double dt, Counters* cnt, hipStream_t s, int sub = -1,
-                             int nsub = 1);
+                             int nsub = 1, bool advance = false);
 hipError_t launch_dense_query(const ClassDev& c, int t0, int nt, int mode, hipStream_t s);
 hipError_t launch_dense_init_thermal(const ClassDev& c, double kT, uint64_t seed, hipStream_t s);
 hipError_t launch_prop(const ClassDev& c, int precision, hipStream_t s);
@@ -392,7 +392,8 @@ hipError_t launch_filter_fused(const ClassSet& set, double dt, uint64_t seed, Co
 hipError_t launch_lowdin(const ClassDev& c, Counters* cnt, int every, double2* scratch,
                          hipStream_t s);
 size_t lowdin_scratch_elems(const ClassDev& c);
-hipError_t launch_advance(Counters* cnt, hipStream_t s);
+hipError_t launch_advance(Counters* cnt, hipStream_t s);  // a step without solves
+hipError_t launch_set_counters(Counters* cnt, int64_t step, int64_t run_step0, int64_t record_every, hipStream_t s);
 hipError_t launch_fill(double* p, size_t count, double value, hipStream_t s);
 // Adjoint along prescribed paths (k_eig.hip, k_adjoint.hip).
 struct AdjTerms {

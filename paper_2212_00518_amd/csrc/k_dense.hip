@@ -63,7 +63,6 @@ struct DenLds {
   double* sg;    // [np]: sign applied to Jacobi column j
   double* rs;    // [np]: row sums of |B| (the Gershgorin interval)
   double* red;   // [2 kDenWaves]: per-wave partial results
-  double* J;     // [kMaxCheb]: Bessel values
   double* nuc;   // [4]: half-step velocity, new position, propagator position, force
   int* rank;     // [np]: position of Jacobi column j in ascending order
   int* pq;       // [np]: the pairs of a round
@@ -74,7 +73,7 @@ struct DenLds {
 __host__ __device__ inline size_t dense_lds_bytes(int np) {
   const size_t ld = np + 1;
   return sizeof(double) * (2 * (size_t)np * ld + 4 * (size_t)np + (size_t)np + 2 * kDenWaves +
-                           kMaxCheb + 4) +
+                           4) +
          sizeof(int) * (2 * (size_t)np + 5);
 }
 
@@ -89,8 +88,7 @@ __device__ __forceinline__ DenLds dense_lds(double* sm, int np) {
   L.sg = L.dj + np;
   L.rs = L.sg + np;
   L.red = L.rs + np;
-  L.J = L.red + 2 * kDenWaves;
-  L.nuc = L.J + kMaxCheb;
+  L.nuc = L.red + 2 * kDenWaves;
   L.rank = reinterpret_cast<int*>(L.nuc + 4);
   L.pq = L.rank + np;
   L.flag = L.pq + np;
@@ -757,11 +755,12 @@ __device__ __forceinline__ void dense_geo(double* geo, const ModelDev& md, doubl
 
 // One step of one trajectory up to the propagation (sub as in k_eig_step:
 // -1 the whole step, j >= 0 the propagator of electronic sub-step j of nsub,
-// -2 the end point only).
+// -2 the end point only).  advance: as in k_eig_fused.
 __global__ __launch_bounds__(kDenThreads) void k_dense_step(ClassDev c, double dt_run, int precision,
-                                                             Counters* cnt, int sub, int nsub) {
+                                                             Counters* cnt, int sub, int nsub, int advance) {
   extern __shared__ double sm[];
   const int t = blockIdx.x, tid = threadIdx.x;
+  if (advance && t == 0 && tid == 0) cnt->step += 1;
   if (t >= live_slots(c) || (c.status[t] & kFreezeMask)) return;
   const ModelDev& md = c.md;
   const int n = md.n, np = md.n_pad, RT = np / 16;
@@ -829,9 +828,10 @@ __global__ __launch_bounds__(kDenThreads) void k_dense_step(ClassDev c, double d
       c.lam_mid[(size_t)t * np + j] = L.lam[j];
     }
     const double lo = block_min(lo_part, L.red), hi = block_max(hi_part, L.red);
-    if (tid == 0) {
+    if (tid < 64) {
       double* cb = c.cheb + (size_t)t * kChebStride;
-      if (write_cheb(cb, lo, hi, dte, precision, cnt, sub <= 0, L.J, c.work) < 0) L.flag[1] |= 2;
+      const int K = write_cheb(cb, lo, hi, dte, precision, cnt, sub <= 0, c.work);
+      if (tid == 0 && K < 0) L.flag[1] |= 2;
     }
     __syncthreads();
     if (sub >= 0) {
@@ -980,14 +980,14 @@ hipError_t set_lds(const void* fn, size_t bytes) {
 size_t dense_lds_size(int n_pad) { return dense_lds_bytes(n_pad); }
 
 hipError_t launch_dense_step(const ClassDev& c, double dt, Counters* cnt, hipStream_t s, int sub,
-                             int nsub) {
+                             int nsub, bool advance) {
   const int precision = c.C64 ? IESH_FP64 : IESH_MIXED;
   if (c.n_live < 1) return hipSuccess;
   const size_t lds = dense_lds_bytes(c.md.n_pad);
   hipError_t e = set_lds((const void*)k_dense_step, lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_dense_step, dim3(c.n_live), dim3(kDenThreads), lds, s, c, dt, precision, cnt,
-                     sub, nsub);
+                     sub, nsub, (int)advance);
   return hipGetLastError();
 }
 

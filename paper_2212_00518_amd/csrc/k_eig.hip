@@ -30,14 +30,15 @@ namespace iesh {
 namespace {
 
 constexpr int kEigThreads = 256;
-static_assert(kEigThreads % 64 == 0, "whole waves: the secular solve relies on it");
+static_assert(kEigThreads == 256, "four whole waves: the secular solve and block_sum rely on it");
 // Register budget of the step kernels: 5 waves per SIMD (at most 96 VGPRs)
-// fit without spills; the LDS of a work-group would allow 7.
+// fit nearly without spills; the LDS of a work-group allows 5.
 constexpr int kEigWavesPerSimd = 5;
 constexpr double kEps = 2.220446049250313e-16;
 
 struct EigLds {
   double e[kMaxStates];      // bath energies
+  double vbar[kMaxStates];   // couplings without their geometry factor
   double V2[kMaxStates];     // V_k(x)^2
   double tau[kMaxStates];    // root relative to its origin pole
   double Vh2[kMaxStates];    // Loewner couplings squared
@@ -50,7 +51,6 @@ struct EigLds {
   int fail;
   int count;
   double sc[16];             // scalars
-  double J[kMaxCheb];        // Bessel values J_0..J_K of the propagator
   double nuc[4][kMaxDof];    // half-step velocity, new, frozen-propagator geometry, force
 };
 
@@ -74,6 +74,17 @@ __device__ inline double rcp_nr1(double d) {
   return fma(r, fma(-d, r, 1.0), r);
 }
 
+// Sum of a value over the work-group, the same in every thread: one barrier and
+// a wave's exchanges.  `red` may be written again after the next barrier.
+__device__ inline double block_sum(double v, double* red) {
+  red[threadIdx.x] = v;
+  __syncthreads();
+  const int l = threadIdx.x & 63;
+  double s = (red[l] + red[l + 128]) + (red[l + 64] + red[l + 192]);
+  for (int sh = 32; sh > 0; sh >>= 1) s += __shfl_down(s, sh);
+  return __shfl(s, 0);
+}
+
 // f and its split derivative at tau (origin eo); terms with k < j are left
 // of the root.  j0 is the same for all lanes of the wave and no lane's j lies
 // outside [j0, j0 + 64), so poles below j0 are left of every lane's root and
@@ -95,6 +106,7 @@ __device__ inline void secular_eval_group(int j, int g, int G, int M, const doub
                                           const double* V2, double eo, double emh, double tau,
                                           double& f, double& dl, double& dr, double& err) {
   double pl = 0.0, pr = 0.0, l = 0.0, r = 0.0;
+#pragma unroll 4
   for (int k = g; k < M; k += G) {
     const double d = (e[k] - eo) - tau;
     const double inv = rcp_nr1(d);
@@ -361,6 +373,26 @@ __device__ inline RootStore root_store(const ClassDev& c, int t) {
                    c.root_geo + 4 * hm};
 }
 
+// The geometry of an earlier solve to start from.
+struct PrevSolve {
+  bool valid = false;
+  double h = 0.0, f = 0.0;
+};
+
+// The stored roots into L (per root, as solve_arrowhead takes them).
+__device__ inline PrevSolve load_roots(const RootStore& rs, int roots, EigLds& L) {
+  for (int j = threadIdx.x; j < roots; j += kEigThreads) {
+    L.tau[j] = rs.tau[j];
+    L.q0[j] = rs.q0[j];
+    L.org[j] = rs.org[j];
+  }
+  PrevSolve p;
+  p.valid = rs.geo[2] == 1.0;
+  p.h = rs.geo[0];
+  p.f = rs.geo[1];
+  return p;
+}
+
 // Solve the arrowhead problem of geometry x; fills lam, tau, org, q0 in LDS
 // (entries n..n_pad-1 of lam/q0 set to 0).  Returns model scalars.
 // The eigenvector of root lambda_j is proportional to (1, V_k / (lambda_j -
@@ -369,48 +401,40 @@ __device__ inline RootStore root_store(const ClassDev& c, int t) {
 // sums are the same ones the root was found from.  kLoewner also leaves the
 // Loewner couplings (the couplings for which the computed roots are exact,
 // which give the bath components of the eigenvectors) in L.Vh2.
-// rs (may be null): warm = start every root from the stored one of the last
-// solve, store = keep this solve's roots there.  By Weyl's inequality each
+// prev (if valid): start every root from the one of an earlier solve at its
+// geometry, which L.tau, L.q0 and L.org hold per root.  rs (may be null): keep
+// this solve's roots there.  By Weyl's inequality each
 // eigenvalue moves by at most ||H' - H||_2 <= |dh| + ||dV|| between the two
 // geometries (the bath energies are fixed and V = Vbar f(x), so
 // ||dV|| = |df| ||Vbar||); with that bound, doubled, every root gets a bracket
 // that contains it, and the safeguarded iteration converges in a couple of
 // steps instead of starting from the gap.
 template <bool kLoewner = false>
-__device__ ModelAt solve_arrowhead(const ModelDev& md, const double* __restrict__ vbar,
-                                   const double* x, EigLds& L, RootStore rs = RootStore{},
-                                   bool warm = false, bool store = false,
+__device__ ModelAt solve_arrowhead(const ModelDev& md, const double* x, EigLds& L,
+                                   PrevSolve prev = PrevSolve{}, RootStore rs = RootStore{},
                                    double accept = kStepAccept) {
   // the secular problem over the distinct bath energies (M = M_red poles,
   // M + 1 roots); repeated energies are expanded into deflated states below
   const int M = md.M_red, n = M + 1, tid = threadIdx.x;
   const ModelAt ma = model_at(md, x);
-  for (int k = tid; k < M; k += kEigThreads) {
-    const double V = vbar[k] * ma.f;
-    L.V2[k] = V * V;
-  }
-  __syncthreads();
-  // ||V||^2 (fixed-order reduction)
   double part = 0.0;
-  for (int k = tid; k < M; k += kEigThreads) part += L.V2[k];
-  L.red[tid] = part;
-  __syncthreads();
-  for (int s = kEigThreads / 2; s > 0; s >>= 1) {
-    if (tid < s) L.red[tid] += L.red[tid + s];
-    __syncthreads();
+  for (int k = tid; k < M; k += kEigThreads) {
+    const double V = L.vbar[k] * ma.f;
+    L.V2[k] = V * V;
+    part += V * V;
   }
-  const double vnorm = sqrt(L.red[0]);
-  __syncthreads();
+  // ||V||^2 (fixed-order reduction)
+  const double vnorm = sqrt(block_sum(part, L.red));
   // warm start: the bound on how far every root moved since the stored solve,
   // and the first-order move of each (q_j^T (H' - H) q_j with the stored
   // vectors: dh q0_j^2 + 2 q0_j^2 (lambda_j - h) df / f, since
   // sum_k V_k Q_kj = (lambda_j - h) q0_j) as the starting point
   double dlt = -1.0, dh0 = 0.0, dfr = 0.0, h0 = 0.0;
-  if (rs.geo && warm && rs.geo[2] == 1.0) {
-    h0 = rs.geo[0];
+  if (prev.valid) {
+    h0 = prev.h;
     dh0 = ma.h - h0;
-    const double df = ma.f - rs.geo[1];
-    dfr = rs.geo[1] != 0.0 ? df / rs.geo[1] : 0.0;  // f = 0: no coupling, no move from V
+    const double df = ma.f - prev.f;
+    dfr = prev.f != 0.0 ? df / prev.f : 0.0;  // f = 0: no coupling, no move from V
     const double bound = fabs(dh0) + fabs(df) * (vnorm / ma.f);
     dlt = 2.0 * bound + 64.0 * kEps * (fabs(ma.h) + vnorm + fabs(L.e[0]) + fabs(L.e[M - 1]));
   }
@@ -429,8 +453,8 @@ __device__ ModelAt solve_arrowhead(const ModelDev& md, const double* __restrict_
     int o;
     double lam_g = 0.0, lam_s = 0.0;
     if (dlt >= 0.0) {
-      lam_g = L.e[rs.org[j]] + rs.tau[j];
-      const double q2 = rs.q0[j] * rs.q0[j];
+      lam_g = L.e[L.org[j]] + L.tau[j];
+      const double q2 = L.q0[j] * L.q0[j];
       lam_s = lam_g + q2 * (dh0 + 2.0 * (lam_g - h0) * dfr);
     }
     double dsum = 0.0;
@@ -442,7 +466,7 @@ __device__ ModelAt solve_arrowhead(const ModelDev& md, const double* __restrict_
       L.lam[j] = L.e[o] + tau;
       L.q0[j] = 1.0 / sqrt(1.0 + dsum);
       if (!ok) atomicOr(&L.fail, 1);
-      if (rs.geo && store) {
+      if (rs.geo) {
         rs.tau[j] = tau;
         rs.q0[j] = L.q0[j];
         rs.org[j] = o;
@@ -450,7 +474,7 @@ __device__ ModelAt solve_arrowhead(const ModelDev& md, const double* __restrict_
     }
   }
   __syncthreads();
-  if (rs.geo && store && tid == 0) {
+  if (rs.geo && tid == 0) {
     rs.geo[0] = ma.h;
     rs.geo[1] = ma.f;
     rs.geo[2] = L.fail ? 0.0 : 1.0;
@@ -547,15 +571,7 @@ __device__ double hf_force(const ModelDev& md, const ModelAt& ma, const int32_t*
     const int a = occ[tid];
     part = L.q0[a] * L.q0[a] * (ma.dh + 2.0 * ma.rho * (L.lam[a] - ma.h));
   }
-  L.red2[tid] = part;
-  __syncthreads();
-  for (int s = kEigThreads / 2; s > 0; s >>= 1) {
-    if (tid < s) L.red2[tid] += L.red2[tid + s];
-    __syncthreads();
-  }
-  const double F = -ma.dU0 - L.red2[0];
-  __syncthreads();
-  return F;
+  return -ma.dU0 - block_sum(part, L.red2);
 }
 
 // Hellmann-Feynman force on every coordinate of the multi-coordinate model at
@@ -611,7 +627,10 @@ __device__ void write_geo_grads(double* geo, const ModelDev& md, const ModelAt& 
 }
 
 __device__ void load_bath(const ClassDev& c, EigLds& L) {
-  for (int k = threadIdx.x; k < c.md.M_red; k += kEigThreads) L.e[k] = c.eps[k];
+  for (int k = threadIdx.x; k < c.md.M_red; k += kEigThreads) {
+    L.e[k] = c.eps[k];
+    L.vbar[k] = c.vbar[k];
+  }
   if (threadIdx.x == 0) {
     L.fail = 0;
     L.count = 0;
@@ -633,7 +652,18 @@ __device__ void cheb_setup(const ClassDev& c, int t, const ModelAt& mm, double v
   double lo_part = 1e300, hi_part = -1e300;
   for (int k = tid; k < n; k += kEigThreads) L.eo[k] = L.e[L.org[k]];
   __syncthreads();
-  for (int j = tid; j < n_pad; j += kEigThreads) {
+  // small orders: a row's columns are dealt to G threads
+  int G = 1;
+  while (2 * G * n_pad <= kEigThreads) G *= 2;
+  const int part = G > 1 ? tid / n_pad : 0;
+  double rsum = 0.0;
+  auto interval = [&](int j) {
+    if (j < n) {
+      lo_part = fmin(lo_part, L.lam[j] - rsum);
+      hi_part = fmax(hi_part, L.lam[j] + rsum);
+    }
+  };
+  for (int j = tid - part * n_pad; j < n_pad && part < G; j += kEigThreads) {
     const int lane_off = ((j >> 4) << 6) + (j & 15);
     // v D[j][k] = q0_k (a_j + b_j (lambda_k - h)) / (lambda_k - lambda_j) with
     // a_j = v q0_j (h' + rho (lambda_j - h)) and b_j = v q0_j rho, since
@@ -644,8 +674,8 @@ __device__ void cheb_setup(const ClassDev& c, int t, const ModelAt& mm, double v
     const double aj = vfac * q0j * (mm.dh + mm.rho * (L.lam[j] - mm.h));
     const double bj = vfac * q0j * mm.rho;
     const double eoj = (j < n) ? L.eo[j] : 0.0, tj = (j < n) ? L.tau[j] : 0.0;
-    double rsum = 0.0;
-    for (int k = 0; k < n_pad; ++k) {
+    rsum = 0.0;
+    for (int k = part; k < n_pad; k += G) {
       double val = 0.0;
       if (k < n) {
         const double num = L.q0[k] * fma(bj, L.lam[k] - mm.h, aj);
@@ -662,26 +692,31 @@ __device__ void cheb_setup(const ClassDev& c, int t, const ModelAt& mm, double v
       else
         (Bt32 + koff)[lane_off] = (float)val;
     }
-    if (j < n) {
-      lo_part = fmin(lo_part, L.lam[j] - rsum);
-      hi_part = fmax(hi_part, L.lam[j] + rsum);
+    if (G == 1) interval(j);
+    if (part == 0) c.lam_mid[(size_t)t * n_pad + j] = (j < n) ? L.lam[j] : 0.0;
+  }
+  if (G > 1) {
+    L.Vh2[tid] = rsum;
+    __syncthreads();
+    if (tid < n_pad) {
+      for (int q = 1; q < G; ++q) rsum += L.Vh2[q * n_pad + tid];
+      interval(tid);
     }
-    c.lam_mid[(size_t)t * n_pad + j] = (j < n) ? L.lam[j] : 0.0;
   }
   L.red[tid] = lo_part;
   L.red2[tid] = hi_part;
   __syncthreads();
-  for (int s = kEigThreads / 2; s > 0; s >>= 1) {
-    if (tid < s) {
-      L.red[tid] = fmin(L.red[tid], L.red[tid + s]);
-      L.red2[tid] = fmax(L.red2[tid], L.red2[tid + s]);
-    }
-    __syncthreads();
+  if (tid >= 64) return;
+  double lo = fmin(fmin(L.red[tid], L.red[tid + 128]), fmin(L.red[tid + 64], L.red[tid + 192]));
+  double hi = fmax(fmax(L.red2[tid], L.red2[tid + 128]), fmax(L.red2[tid + 64], L.red2[tid + 192]));
+  for (int sh = 32; sh > 0; sh >>= 1) {
+    lo = fmin(lo, __shfl_xor(lo, sh));
+    hi = fmax(hi, __shfl_xor(hi, sh));
   }
+  double* cb = c.cheb + (size_t)t * kChebStride;
+  const int K = write_cheb(cb, lo, hi, dte, precision, cnt, count_step, c.work);
   if (tid == 0) {
-    double* cb = c.cheb + (size_t)t * kChebStride;
-    if (write_cheb(cb, L.red[0], L.red2[0], dte, precision, cnt, count_step, L.J, c.work) < 0)
-      atomicOr(&L.fail, 2);
+    if (K < 0) atomicOr(&L.fail, 2);
     if (c.ips) {
       c.ips[(size_t)t * kIpStride + IP_SUB] = 0.0f;
       c.chebq[2 + atomicAdd(&c.chebq[0], 1)] = t;
@@ -966,14 +1001,28 @@ template <bool kIp>
 __device__ void eig_step_one(const ClassDev& c, int t, double dt_run, int precision, Counters* cnt,
                              int sub, int nsub, EigLds& L) {
   const int tid = threadIdx.x;
-  if (t >= live_slots(c) || (c.status[t] & kFreezeMask)) return;
-  const double dt = c.clock ? c.clock[2 * (size_t)t] : dt_run;  // this trajectory's step
   const ModelDev& md = c.md;
-  load_bath(c, L);
   const int nd = md.ndof;
+  // what the step starts from, requested together
+  const int live = live_slots(c), status = c.status[t];
+  const bool stored = c.root_tau && !c.path;
+  RootStore rs{};
+  if (stored) rs = root_store(c, t);
+  double x = 0.0, v = 0.0, F = 0.0;
+  if (tid < nd && !c.path) {
+    x = c.x[(size_t)t * nd + tid];
+    v = c.v[(size_t)t * nd + tid];
+    F = c.F[(size_t)t * nd + tid];
+  }
+  const double dt = c.clock ? c.clock[2 * (size_t)t] : dt_run;  // this trajectory's step
+  if (t >= live || (status & kFreezeMask)) return;
+  // warm starts from the trajectory's previous solve (not along prescribed
+  // paths, whose backward pass revisits steps out of order)
+  PrevSolve prev;
+  if (stored) prev = load_roots(rs, md.M_red + 1, L);
   if (tid < nd) {
     const int nu = tid;
-    double vh, xn, x;
+    double vh, xn;
     if (c.path) {
       // prescribed path (one coordinate): v over the step from the two end points
       const double* pp = c.path + (size_t)c.gtraj[t] * c.path_len + c.path_n;
@@ -981,8 +1030,6 @@ __device__ void eig_step_one(const ClassDev& c, int t, double dt_run, int precis
       xn = pp[1];
       vh = (xn - x) / dt;
     } else {
-      x = c.x[(size_t)t * nd + nu];
-      const double v = c.v[(size_t)t * nd + nu], F = c.F[(size_t)t * nd + nu];
       vh = v + 0.5 * dt * F / md.mass_dof[nu];
       xn = x + dt * vh;
     }
@@ -990,22 +1037,23 @@ __device__ void eig_step_one(const ClassDev& c, int t, double dt_run, int precis
     L.nuc[1][nu] = xn;
     L.nuc[2][nu] = (sub >= 0) ? x + ((sub + 0.5) / nsub) * (xn - x) : 0.5 * (x + xn);
   }
-  __syncthreads();
+  load_bath(c, L);
   const double vh = L.nuc[0][0];
   const double dte = (sub >= 0) ? dt / nsub : dt;  // electronic step of this propagator
 
   const int n_pad = md.n_pad;
   if (sub != -2) {
   // ---- midpoint geometry: couplings for the propagator
-  // warm starts from the trajectory's previous solve (not along prescribed
-  // paths, whose backward pass revisits steps out of order)
-  const bool warm = c.root_tau && !c.path;
   // the mixed path's step solves stop the secular iteration earlier (not
   // along prescribed paths, whose gradients are FP64)
   const double accept = (precision == IESH_FP64 || c.path) ? kStepAccept : kStepAcceptMixed;
-  RootStore rs{};
-  if (warm) rs = root_store(c, t);
-  ModelAt mm = solve_arrowhead(md, c.vbar, L.nuc[2], L, rs, warm, warm, accept);
+  // the end point's solve starts from these roots: where L keeps them as they
+  // are (no deflated states in between), they need not be stored
+  const bool keep = sub == -1 && !md.expand;
+  ModelAt mm = solve_arrowhead(md, L.nuc[2], L, prev, keep ? RootStore{} : rs, accept);
+  prev.valid = stored && !L.fail;
+  prev.h = mm.h;
+  prev.f = mm.f;
   double vfac = vh;
   if (nd > 1) {
     // v . D over the coordinates: the gradients enter through v.grad h and v.grad f / f
@@ -1032,10 +1080,11 @@ __device__ void eig_step_one(const ClassDev& c, int t, double dt_run, int precis
   }
 
   // ---- end-point geometry: energies, amplitudes, forces
-  const bool warm_end = c.root_tau && !c.path;
-  RootStore rse{};
-  if (warm_end) rse = root_store(c, t);
-  const ModelAt mn = solve_arrowhead(md, c.vbar, L.nuc[1], L, rse, warm_end, warm_end,
+  if (stored && md.expand && sub == -1) {
+    prev = load_roots(rs, md.M_red + 1, L);
+    __syncthreads();
+  }
+  const ModelAt mn = solve_arrowhead(md, L.nuc[1], L, prev, rs,
                                      (precision == IESH_FP64 || c.path) ? kStepAccept : kStepAcceptMixed);
   for (int j = tid; j < n_pad; j += kEigThreads) {
     c.lam[(size_t)t * n_pad + j] = L.lam[j];
@@ -1077,12 +1126,15 @@ __global__ __launch_bounds__(kEigThreads) __attribute__((amdgpu_waves_per_eu(kEi
 // on slot b - first[k] of class k (first[k] <= b < first[k + 1]).  The classes
 // come largest first, so the dispatcher hands out the long work-groups
 // first and the small classes fill the compute units behind them.
+// advance: the first launch of a step, which moves the step counter on (the
+// solves don't read it).
 // kIp: the mixed path, whose trajectories propagate in the interaction picture.
 template <bool kIp>
 __global__ __launch_bounds__(kEigThreads) __attribute__((amdgpu_waves_per_eu(kEigWavesPerSimd))) void k_eig_fused(ClassSet set, double dt_run, int precision,
-                                                            Counters* cnt, int sub, int nsub) {
+                                                            Counters* cnt, int sub, int nsub, int advance) {
   __shared__ EigLds L;
   const int b = blockIdx.x;
+  if (advance && b == 0 && threadIdx.x == 0) cnt->step += 1;
   int k = 0;
   while (k + 1 < set.n && b >= set.first[k + 1]) ++k;
   eig_step_one<kIp>(set.c[k], b - set.first[k], dt_run, precision, cnt, sub, nsub, L);
@@ -1105,7 +1157,7 @@ __global__ __launch_bounds__(kEigThreads) void k_eig_query(ClassDev c, int t0, i
   RootStore rs{};
   const bool store = mode == 1 && c.root_tau && !c.path;
   if (store) rs = root_store(c, t);
-  const ModelAt ma = solve_arrowhead(md, c.vbar, L.nuc[1], L, rs, false, store);
+  const ModelAt ma = solve_arrowhead(md, L.nuc[1], L, PrevSolve{}, rs);
   for (int j = tid; j < md.n_pad; j += kEigThreads) {
     c.lam[(size_t)t * md.n_pad + j] = L.lam[j];
     c.q0[(size_t)t * md.n_pad + j] = L.q0[j];
@@ -1181,7 +1233,7 @@ __global__ __launch_bounds__(kEigThreads) void k_init_thermal(ClassDev c, double
   RootStore rs{};
   const bool store = c.root_tau && !c.path;
   if (store) rs = root_store(c, t);
-  const ModelAt ma = solve_arrowhead<true>(md, c.vbar, L.nuc[1], L, rs, false, store);
+  const ModelAt ma = solve_arrowhead<true>(md, L.nuc[1], L, PrevSolve{}, rs);
   int32_t* occ = c.occ + (size_t)t * N;
   __shared__ int chosen[kMaxStates];
   bool done = false;
@@ -1288,19 +1340,6 @@ __device__ inline double lam_minus_eps(const EigLds& L, int j, int k) {
   return -((L.e[k] - L.e[L.org[j]]) - L.tau[j]);
 }
 
-__device__ double block_sum(double v, double* red) {
-  const int tid = threadIdx.x;
-  red[tid] = v;
-  __syncthreads();
-  for (int s = kEigThreads / 2; s > 0; s >>= 1) {
-    if (tid < s) red[tid] += red[tid + s];
-    __syncthreads();
-  }
-  const double r = red[0];
-  __syncthreads();
-  return r;
-}
-
 // Accumulate into grad the parameter cotangents of one eigen-solve at x whose
 // (lambda, q0) cotangents are in A.lbar, A.qbar, plus hpbar for h' = dh/dx.
 __device__ void eig_backprop(const ModelDev& md, const ModelAt& ma, double x, AdjLds& A,
@@ -1323,6 +1362,7 @@ __device__ void eig_backprop(const ModelDev& md, const ModelAt& ma, double x, Ad
   double hpart = 0.0;
   for (int j = tid; j < n; j += kEigThreads) hpart += A.lbar[j] * L.q0[j] * L.q0[j];
   const double hbar = block_sum(hpart, A.red3);
+  __syncthreads();
   double gpart = 0.0;
   for (int k = tid; k < M; k += kEigThreads) {
     const double V = sqrt(L.V2[k]);
@@ -1368,7 +1408,7 @@ __global__ __launch_bounds__(kEigThreads) void k_adj_explicit(ClassDev c, const 
   const double w = weights[c.gtraj[t]];
   const double x = c.path[(size_t)c.gtraj[t] * c.path_len + s];
   load_bath(c, L);
-  const ModelAt ma = solve_arrowhead(md, c.vbar, &x, L);
+  const ModelAt ma = solve_arrowhead(md, &x, L);
   const double* C = Cs + (size_t)t * N * n_pad * 2;
   double* G = Gh + (size_t)t * N * n_pad * 2;
   // z_o = sum_a q0_a C[o][a], one wave per orbital
@@ -1449,7 +1489,7 @@ __global__ __launch_bounds__(kEigThreads) void k_adj_mid(ClassDev c, const doubl
   const double xm = 0.5 * (x0 + x1), v = (x1 - x0) / dt;
   const double r = 1.0 / c.cheb[(size_t)t * kChebStride + CHEB_INVR];
   load_bath(c, L);
-  const ModelAt ma = solve_arrowhead(md, c.vbar, &xm, L);
+  const ModelAt ma = solve_arrowhead(md, &xm, L);
   const double hp = ma.dh;
   const double* P = imphi + (size_t)t * n_pad * n_pad;
   const double sc = 2.0 * v / r;  // Dbar = sc * Im Phi
@@ -1496,14 +1536,14 @@ hipError_t launch_eig_step(const ClassDev& c, double dt, Counters* cnt, hipStrea
 }
 
 hipError_t launch_eig_fused(const ClassSet& set, double dt, int precision, Counters* cnt, hipStream_t s,
-                            int sub, int nsub) {
+                            int sub, int nsub, bool advance) {
   if (set.n < 1 || set.first[set.n] < 1) return hipSuccess;
   if (precision == IESH_FP64)
     hipLaunchKernelGGL(k_eig_fused<false>, dim3(set.first[set.n]), dim3(kEigThreads), 0, s, set, dt, precision,
-                       cnt, sub, nsub);
+                       cnt, sub, nsub, (int)advance);
   else
     hipLaunchKernelGGL(k_eig_fused<true>, dim3(set.first[set.n]), dim3(kEigThreads), 0, s, set, dt, precision,
-                       cnt, sub, nsub);
+                       cnt, sub, nsub, (int)advance);
   return hipGetLastError();
 }
 

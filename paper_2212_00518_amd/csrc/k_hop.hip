@@ -1146,6 +1146,7 @@ __global__ __launch_bounds__(kMmThreads) void k_hop_mm(ClassDev c, double dt, ui
   int32_t* q = c.hopq;
   const int b = blockIdx.x;
   const int n_items = query_mode ? 1 : q[0];
+  if (n_items == 0) return;  // an empty queue has nothing to reset
   for (int e = query_mode ? 0 : b; e < n_items; e += gridDim.x) {
     const int t = query_mode ? t0 + b : q[3 + e];
     hop_one_mm<kF32, kDense>(c, t, dt, seed, cnt, events, query_mode, record, exit_enabled, exit_x,
@@ -1175,6 +1176,7 @@ __global__ __launch_bounds__(kHopThreads) void k_hop(ClassDev c, double dt, uint
   const int b = blockIdx.x;
   // persistent: entries b, b + G, b + 2G, ... of the queue (G the grid)
   const int n_items = query_mode ? 1 : q[0];
+  if (n_items == 0) return;  // an empty queue has nothing to reset
   for (int e = query_mode ? 0 : b; e < n_items; e += gridDim.x) {
     const int t = query_mode ? t0 + b : q[3 + e];
     double2* xscr = x_via_scratch<kRS, kRB>() ? c.hopx + (size_t)t * c.md.N * c.md.N : nullptr;
@@ -1436,6 +1438,12 @@ __global__ __launch_bounds__(kFltThreads) void k_filter_fused(ClassSet set, doub
                            max_steps, delta, L);
 }
 
+__global__ void k_set_counters(Counters* cnt, int64_t step, int64_t run_step0, int64_t record_every) {
+  cnt->step = step;
+  cnt->run_step0 = run_step0;
+  cnt->record_every = record_every;
+}
+
 __global__ void k_advance(Counters* cnt) {
   if (threadIdx.x == 0 && blockIdx.x == 0) cnt->step = cnt->step + 1;
 }
@@ -1642,6 +1650,11 @@ hipError_t launch_filter_fused(const ClassSet& set, double dt, uint64_t seed, Co
       IESH_FUSED(true, false);
   }
 #undef IESH_FUSED
+  return hipGetLastError();
+}
+
+hipError_t launch_set_counters(Counters* cnt, int64_t step, int64_t run_step0, int64_t record_every, hipStream_t s) {
+  hipLaunchKernelGGL(k_set_counters, dim3(1), dim3(1), 0, s, cnt, step, run_step0, record_every);
   return hipGetLastError();
 }
 

@@ -410,6 +410,7 @@ template <int kQ>
 __global__ __launch_bounds__(kPropThreads) void k_prop_queue(ClassDev c) {
   extern __shared__ unsigned char smem_raw[];
   const int items = c.chebq[0] * c.n_slabs;
+  if (items == 0) return;  // nothing to reset either (14 us with the count of the work-groups done, 4 without)
   for (int i = blockIdx.x; i < items; i += gridDim.x) {
     prop_item<float, kPropagate, kQ>(c, nullptr, 0, c.chebq[2 + i / c.n_slabs], i % c.n_slabs, smem_raw);
     __syncthreads();

@@ -83,3 +83,30 @@ def test_mixed_propagator_product_counts():
         counts[f] = ens.work()[0]
         ens.close()
     assert counts[0.0] <= 2 and 2 <= counts[1.0] <= 4 and counts[60.0] >= 8, counts
+
+
+# rows of the coupling matrix dealt to 8, 4, 2 and 1 threads and two rows a
+# thread; series of 1 to about 60 terms
+@pytest.mark.parametrize("dt_factor", [1e-6, 0.3, 1.0, 8.0, 18.0])
+@pytest.mark.parametrize("M,N", [(1, 1), (15, 8), (31, 9), (40, 20), (64, 20), (127, 40), (200, 20), (300, 12)])
+def test_fp64_series_over_orders_and_terms(M, N, dt_factor):
+    """One FP64 step against the oracle's exponential: the series' tail and
+    the roundings of up to 63 terms, the roots' 3e-15 times the phase (18 at most)
+    and the oracle's own rounding: below 1e-12."""
+    cfg = make_cfg("c2", M=M, N=N)
+    cfg["dt"] *= dt_factor
+    m = models.from_config(cfg, M=M)
+    states = random_states(m, N, 3, seed=77 + M, xs=[-2.0, 1.0, 6.0], v_scale=7e-4 / max(1.0, dt_factor))
+    ens = ensemble(cfg, 3)
+    upload(ens, states)
+    ens.step()
+    x, v, C, occ = ens.get_state()
+    assert np.all(ens.status() == 0)
+    from paper_2212_00518_amd import unpack_C
+    for t in range(3):
+        F = dyn.el.forces(m, states[t].x, states[t].s)
+        ref = dyn.step(m, states[t], cfg["dt"], 2.0, F)[0]
+        err = np.max(np.abs(unpack_C(C, t, m.n, N, ens.n_max, ens.N_max) - ref.C))
+        print(f"M={M} dt x {dt_factor}: |dC| {err:.2e}", flush=True)
+        assert err <= 1e-12
+    ens.close()
