@@ -5,6 +5,7 @@
 #include <cstdio>
 #include <cstring>
 #include <new>
+#include <memory>
 #include <string>
 #include <vector>
 
@@ -937,10 +938,21 @@ int iesh_create(const iesh_model_desc* models, int32_t n_models, const int32_t* 
     const int nd = c.md.ndof;
     const bool dense = d.kind == IESH_MODEL_DENSE;
     c.b_stride = (size_t)n_pad * n_pad;
+    // the state in one allocation, which iesh_get_state copies at once:
+    // orbitals, x, v, occupations
+    const size_t cbytes = (size_t)T * N * n_pad * 2 * (r.precision == IESH_FP64 ? sizeof(double) : sizeof(float));
+    unsigned char* st = nullptr;
+    if ((rc = dalloc(ctx, &st, cbytes + (size_t)T * nd * 2 * sizeof(double) + (size_t)T * N * sizeof(int32_t))))
+      return bail(rc);
+    if (r.precision == IESH_FP64)
+      c.C64 = reinterpret_cast<double*>(st);
+    else
+      c.C32 = reinterpret_cast<float*>(st);
+    c.x = reinterpret_cast<double*>(st + cbytes);
+    c.v = c.x + (size_t)T * nd;
+    c.occ = reinterpret_cast<int32_t*>(c.v + (size_t)T * nd);
     if ((rc = dalloc(ctx, &c.eps, M)) || (rc = dalloc(ctx, &c.vbar, M)) ||
-        (rc = dalloc(ctx, &c.x, (size_t)T * nd)) || (rc = dalloc(ctx, &c.v, (size_t)T * nd)) ||
-        (rc = dalloc(ctx, &c.F, (size_t)T * nd)) ||
-        (rc = dalloc(ctx, &c.occ, (size_t)T * N)) || (rc = dalloc(ctx, &c.status, T)) ||
+        (rc = dalloc(ctx, &c.F, (size_t)T * nd)) || (rc = dalloc(ctx, &c.status, T)) ||
         (rc = dalloc(ctx, &c.gtraj, T)) || (rc = dalloc(ctx, &c.nsteps, T)) ||
         (rc = dalloc(ctx, &c.home, T)) || (rc = dalloc(ctx, &c.stepcap, T)) ||
         (rc = dalloc(ctx, &c.lam, (size_t)T * n_pad)) || (rc = dalloc(ctx, &c.q0, (size_t)T * n_pad)) ||
@@ -1008,9 +1020,7 @@ int iesh_create(const iesh_model_desc* models, int32_t n_models, const int32_t* 
       }
     }
     if (r.precision == IESH_FP64) {
-      if ((rc = dalloc(ctx, &c.C64, (size_t)T * N * n_pad * 2)) ||
-          (rc = dalloc(ctx, &c.Bt, (size_t)T * c.b_stride)))
-        return bail(rc);
+      if ((rc = dalloc(ctx, &c.Bt, (size_t)T * c.b_stride))) return bail(rc);
     } else {
       if (!dense) {
         // the interaction picture's M (f16 pairs) shares the buffer of B
@@ -1023,8 +1033,7 @@ int iesh_create(const iesh_model_desc* models, int32_t n_models, const int32_t* 
           return (fail(ctx, IESH_EDEVICE, "propagation LDS attribute"), bail(IESH_EDEVICE));
         c.cheb_groups = 4 * ctx->n_cu;
       }
-      if ((rc = dalloc(ctx, &c.C32, (size_t)T * N * n_pad * 2)) ||
-          (rc = dalloc(ctx, &c.Bt32, (size_t)T * c.b_stride)) ||
+      if ((rc = dalloc(ctx, &c.Bt32, (size_t)T * c.b_stride)) ||
           (rc = dalloc(ctx, &c.low, lowdin_scratch_elems(c))) ||
           (rc = dalloc(ctx, &c.defect, (size_t)T)))
         return bail(rc);
@@ -1202,65 +1211,63 @@ int iesh_get_state(iesh_ctx* ctx, double* x, double* v, double* C, int32_t* occ,
     return fail(ctx, IESH_EINVAL, "mem_kind");
   HIPTRY(ctx, hipStreamSynchronize(ctx->stream));
   const int T = ctx->run.n_traj;
-  const size_t csize = (size_t)T * ctx->n_max * ctx->N_max * 2;
+  const size_t cbig = (size_t)ctx->n_max * ctx->N_max * 2;  // one trajectory's orbitals
   const int nd = ctx->ndof;
-  std::vector<double> hx((size_t)T * nd), hv((size_t)T * nd), hC(C ? csize : 0, 0.0);
-  std::vector<int32_t> hocc(occ ? (size_t)T * ctx->N_max : 0, -1);
+  // host arrays are filled in place, device ones through a copy
+  const bool dev = mem_kind == IESH_MEM_DEVICE;
+  std::vector<double> bx(dev && x ? (size_t)T * nd : 0), bv(dev && v ? (size_t)T * nd : 0), bC(dev && C ? T * cbig : 0);
+  std::vector<int32_t> bocc(dev && occ ? (size_t)T * ctx->N_max : 0);
+  double *hx = dev && x ? bx.data() : x, *hv = dev && v ? bv.data() : v, *hC = dev && C ? bC.data() : C;
+  int32_t* hocc = dev && occ ? bocc.data() : occ;
   for (size_t ci = 0; ci < ctx->cls.size(); ++ci) {
     ClassDev& c = ctx->cls[ci];
     const int Tc = c.n_traj, N = c.md.N, n = c.md.n, n_pad = c.md.n_pad;
     if (!Tc) continue;
-    std::vector<double> cx((size_t)Tc * nd), cv((size_t)Tc * nd);
-    std::vector<int32_t> cocc((size_t)Tc * N);
-    HIPTRY(ctx, hipMemcpy(cx.data(), c.x, cx.size() * sizeof(double), hipMemcpyDeviceToHost));
-    HIPTRY(ctx, hipMemcpy(cv.data(), c.v, cv.size() * sizeof(double), hipMemcpyDeviceToHost));
-    HIPTRY(ctx, hipMemcpy(cocc.data(), c.occ, cocc.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
-    std::vector<double> cC;
-    if (C) {
-      cC.resize((size_t)Tc * N * n_pad * 2);
-      if (ctx->run.precision == IESH_FP64) {
-        HIPTRY(ctx, hipMemcpy(cC.data(), c.C64, cC.size() * sizeof(double), hipMemcpyDeviceToHost));
-      } else {
-        std::vector<float> f(cC.size());
-        HIPTRY(ctx, hipMemcpy(f.data(), c.C32, f.size() * sizeof(float), hipMemcpyDeviceToHost));
-        for (size_t q = 0; q < f.size(); ++q) cC[q] = f[q];
-      }
-    }
+    // orbitals, x, v and occupations lie in one allocation (iesh_create): one copy
+    const bool f64 = ctx->run.precision == IESH_FP64;
+    const size_t cb = C ? (size_t)Tc * N * n_pad * 2 * (f64 ? sizeof(double) : sizeof(float)) : 0;
+    const size_t xb = (size_t)Tc * nd * sizeof(double), ob = (size_t)Tc * N * sizeof(int32_t);
+    const size_t bytes = cb + 2 * xb + ob;
+    const std::unique_ptr<unsigned char[]> raw(new (std::nothrow) unsigned char[bytes]);
+    if (!raw) return fail(ctx, IESH_ENOMEM, "host memory for the state");
+    HIPTRY(ctx, hipMemcpy(raw.get(), reinterpret_cast<const unsigned char*>(c.x) - cb, bytes, hipMemcpyDeviceToHost));
+    const double* cx = reinterpret_cast<const double*>(raw.get() + cb);
+    const double* cv = cx + (size_t)Tc * nd;
+    const int32_t* cocc = reinterpret_cast<const int32_t*>(cv + (size_t)Tc * nd);
     for (int sl = 0; sl < Tc; ++sl) {
       const int t = ctx->members[ci][ctx->slot_home[ci][sl]];
-      const int tl = sl;
       for (int nu = 0; nu < nd; ++nu) {
-        hx[(size_t)t * nd + nu] = cx[(size_t)tl * nd + nu];
-        hv[(size_t)t * nd + nu] = cv[(size_t)tl * nd + nu];
+        if (hx) hx[(size_t)t * nd + nu] = cx[(size_t)sl * nd + nu];
+        if (hv) hv[(size_t)t * nd + nu] = cv[(size_t)sl * nd + nu];
       }
-      if (occ)
-        for (int r = 0; r < N; ++r) hocc[(size_t)t * ctx->N_max + r] = cocc[(size_t)tl * N + r];
-      if (C) {
-        double* dst = hC.data() + (size_t)t * ctx->n_max * ctx->N_max * 2;
-        for (int j = 0; j < N; ++j)
-          for (int i = 0; i < n; ++i) {
-            const size_t s = (((size_t)tl * N + j) * n_pad + i) * 2;
-            dst[((size_t)j * n + i) * 2] = cC[s];
-            dst[((size_t)j * n + i) * 2 + 1] = cC[s + 1];
-          }
+      if (hocc) {
+        int32_t* dst = hocc + (size_t)t * ctx->N_max;
+        std::copy(cocc + (size_t)sl * N, cocc + (size_t)(sl + 1) * N, dst);
+        std::fill(dst + N, dst + ctx->N_max, -1);
+      }
+      if (hC) {
+        double* dst = hC + t * cbig;
+        for (int j = 0; j < N; ++j) {
+          const size_t s = ((size_t)sl * N + j) * n_pad * 2;
+          if (f64)
+            std::copy_n(reinterpret_cast<const double*>(raw.get()) + s, 2 * n, dst + (size_t)j * n * 2);
+          else
+            std::copy_n(reinterpret_cast<const float*>(raw.get()) + s, 2 * n, dst + (size_t)j * n * 2);
+        }
+        std::fill(dst + (size_t)N * n * 2, dst + cbig, 0.0);
       }
     }
   }
+  if (!dev) return IESH_OK;
   auto put = [&](void* dst, const void* src, size_t bytes) -> int {
-    if (!dst) return IESH_OK;
-    if (mem_kind == IESH_MEM_DEVICE) {
-      HIPTRY(ctx, hipMemcpy(dst, src, bytes, hipMemcpyHostToDevice));
-    } else {
-      std::memcpy(dst, src, bytes);
-    }
+    if (dst) HIPTRY(ctx, hipMemcpy(dst, src, bytes, hipMemcpyHostToDevice));
     return IESH_OK;
   };
   int rc;
-  if ((rc = put(x, hx.data(), hx.size() * sizeof(double)))) return rc;
-  if ((rc = put(v, hv.data(), hv.size() * sizeof(double)))) return rc;
-  if ((rc = put(C, hC.data(), hC.size() * sizeof(double)))) return rc;
-  if ((rc = put(occ, hocc.data(), hocc.size() * sizeof(int32_t)))) return rc;
-  return IESH_OK;
+  if ((rc = put(x, bx.data(), bx.size() * sizeof(double)))) return rc;
+  if ((rc = put(v, bv.data(), bv.size() * sizeof(double)))) return rc;
+  if ((rc = put(C, bC.data(), bC.size() * sizeof(double)))) return rc;
+  return put(occ, bocc.data(), bocc.size() * sizeof(int32_t));
 }
 
 int iesh_step(iesh_ctx* ctx) {
