@@ -614,6 +614,7 @@ int enqueue_step(iesh_ctx* ctx, int record) {
     for (auto& c : ctx->cls)
       if (c.n_traj)
         HIPTRY(ctx, timed(ctx, IESH_TIMER_PROP, [&] {
+                 if (c.i8_slabs) return launch_prop_i8(c, s);
                  if (!c.ips) return launch_prop(c, r.precision, s);
                  const hipError_t e = launch_prop_ip(c, s);
                  return e == hipSuccess ? launch_prop_queue(c, s) : e;
@@ -1020,6 +1021,11 @@ int iesh_create(const iesh_model_desc* models, int32_t n_models, const int32_t* 
       }
     }
     if (r.precision == IESH_FP64) {
+      if (!dense) {
+        c.b_stride = std::max(c.b_stride, i8_b_doubles(n_pad));
+        if (i8_prepare(c) != hipSuccess)
+          return (fail(ctx, IESH_EDEVICE, "propagation LDS attribute"), bail(IESH_EDEVICE));
+      }
       if ((rc = dalloc(ctx, &c.Bt, (size_t)T * c.b_stride))) return bail(rc);
     } else {
       if (!dense) {

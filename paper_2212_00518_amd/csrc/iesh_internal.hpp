@@ -42,7 +42,7 @@ enum GeoSlot {
 // Chebyshev parameter block (layout of cheb[]): [0] centre c, [1] 1/radius,
 // [2] number of terms K (as double), [3] radius*dt, then K complex
 // coefficients (re, im) starting at [8].
-enum ChebSlot { CHEB_C = 0, CHEB_INVR = 1, CHEB_K = 2, CHEB_RHO = 3, CHEB_COEF = 8 };
+enum ChebSlot { CHEB_C = 0, CHEB_INVR = 1, CHEB_K = 2, CHEB_RHO = 3, CHEB_BSCALE = 4, CHEB_COEF = 8 };
 
 // Interaction-picture propagation of the mixed path (k_eig.hip sets it up,
 // prop_ip.hpp applies it).  Per trajectory ips[] holds IP_SUB sub-intervals
@@ -101,6 +101,7 @@ struct ClassDev {
   int traj_offset;      // first global trajectory index of this class
   int nct_max;          // column tiles per propagation work-group
   int n_slabs;          // propagation work-groups per trajectory
+  int i8_slabs = 0;     // the same of the FP64 propagation in 8-bit digits (0: the class does not use it)
   // [T][ceil(N / 8)][n_pad]: for propagation slab s of trajectory t, the
   // squared norms over the slab's orbitals of every row of C after the last
   // propagation (sum_j |C[i][j]|^2), read by the no-hop bound
@@ -133,7 +134,7 @@ struct ClassDev {
   double* lam_mid = nullptr;  // [T][n_pad]
   double* geo = nullptr;    // [T][kGeoStride]
   double* cheb = nullptr;   // [T][kChebStride]
-  double* Bt = nullptr;     // [T][n_pad/4][n_pad/16][64] v*D at the midpoint, MFMA A-tile order
+  double* Bt = nullptr;     // [T][n_pad/4][n_pad/16][64] v*D at the midpoint, MFMA A-tile order (or in 8-bit digits)
   float* Bt32 = nullptr;    // same in FP32 (mixed path), or M in f16 pairs (interaction picture)
   size_t b_stride = 0;      // elements of Bt / Bt32 per trajectory
   // interaction-picture propagation (mixed arrowhead classes, else nullptr)
@@ -379,6 +380,10 @@ int prop_max_col_tiles(int precision);
 int hop_resident_groups(const ClassDev& c, int precision, int n_cu);
 int prop_max_tiles_per_wave(int precision);
 hipError_t prop_prepare(const ClassDev& c, int precision);
+// FP64 propagation in 8-bit digits: sets i8_slabs where the class takes it; its B per trajectory
+size_t i8_b_doubles(int n_pad);
+hipError_t i8_prepare(ClassDev& c);
+hipError_t launch_prop_i8(const ClassDev& c, hipStream_t s);
 size_t prop_lds_bytes(const ClassDev& c, int precision);
 hipError_t launch_hop(const ClassDev& c, double dt, uint64_t seed, Counters* cnt,
                       iesh_event* events, int query_mode, int t0, int nt, int record,

@@ -25,6 +25,7 @@
 
 #include "iesh_cheb.hpp"
 #include "iesh_internal.hpp"
+#include "prop_i8.hpp"
 
 namespace iesh {
 namespace {
@@ -652,6 +653,44 @@ __device__ void cheb_setup(const ClassDev& c, int t, const ModelAt& mm, double v
   double lo_part = 1e300, hi_part = -1e300;
   for (int k = tid; k < n; k += kEigThreads) L.eo[k] = L.e[L.org[k]];
   __syncthreads();
+  // the FP64 classes' B in 8-bit digits (not along prescribed paths, whose
+  // other products take B itself): scaled by a power of two above every
+  // element, |B_jk| <= |a| m1 + 2 |b| sqrt(m1 m2) with the maxima of q0^2 and
+  // (q0 mu)^2 over the gap to the nearest neighbour
+  const bool digits = c.i8_slabs && !c.path;
+  double bscale = 1.0, iscale = 1.0;
+  if (digits) {
+    double m1 = 0.0, m2 = 0.0;
+    for (int j = tid; j < n; j += kEigThreads) {
+      const double q = L.q0[j], mu = L.lam[j] - mm.h;
+      if (q == 0.0) continue;
+      double gap = 1e300;
+      int k = j - 1;
+      while (k >= 0 && L.q0[k] == 0.0) --k;  // deflated states couple to nothing
+      if (k >= 0) gap = (L.eo[j] - L.eo[k]) + (L.tau[j] - L.tau[k]);
+      k = j + 1;
+      while (k < n && L.q0[k] == 0.0) ++k;
+      if (k < n) gap = fmin(gap, (L.eo[k] - L.eo[j]) + (L.tau[k] - L.tau[j]));
+      m1 = fmax(m1, q * q / gap);
+      m2 = fmax(m2, q * q * mu * mu / gap);
+    }
+    L.red[tid] = m1;
+    L.red2[tid] = m2;
+    __syncthreads();
+    const int l = tid & 63;
+    m1 = fmax(fmax(L.red[l], L.red[l + 128]), fmax(L.red[l + 64], L.red[l + 192]));
+    m2 = fmax(fmax(L.red2[l], L.red2[l + 128]), fmax(L.red2[l + 64], L.red2[l + 192]));
+    for (int sh = 32; sh > 0; sh >>= 1) {
+      m1 = fmax(m1, __shfl_xor(m1, sh));
+      m2 = fmax(m2, __shfl_xor(m2, sh));
+    }
+    __syncthreads();
+    int ex = 0;
+    (void)frexp(fabs(vfac * mm.dh) * m1 + 2.0 * fabs(vfac * mm.rho) * sqrt(m1 * m2), &ex);
+    ex = min(max(ex, -900), 900);
+    bscale = ldexp(1.0, ex);
+    iscale = ldexp(1.0, -ex);
+  }
   // small orders: a row's columns are dealt to G threads
   int G = 1;
   while (2 * G * n_pad <= kEigThreads) G *= 2;
@@ -674,14 +713,37 @@ __device__ void cheb_setup(const ClassDev& c, int t, const ModelAt& mm, double v
     const double aj = vfac * q0j * (mm.dh + mm.rho * (L.lam[j] - mm.h));
     const double bj = vfac * q0j * mm.rho;
     const double eoj = (j < n) ? L.eo[j] : 0.0, tj = (j < n) ? L.tau[j] : 0.0;
+    auto element = [&](int k) -> double {
+      if (k >= n) return 0.0;
+      const double num = L.q0[k] * fma(bj, L.lam[k] - mm.h, aj);
+      const double dif = (L.eo[k] - eoj) + (L.tau[k] - tj);  // lambda_k - lambda_j
+      return (num == 0.0 || k == j) ? 0.0 : num * rcp_nr1(dif);
+    };
     rsum = 0.0;
-    for (int k = part; k < n_pad; k += G) {
-      double val = 0.0;
-      if (k < n) {
-        const double num = L.q0[k] * fma(bj, L.lam[k] - mm.h, aj);
-        const double dif = (L.eo[k] - eoj) + (L.tau[k] - tj);  // lambda_k - lambda_j
-        val = (num == 0.0 || k == j) ? 0.0 : num * rcp_nr1(dif);
+    if (digits) {
+      // a lane's 16 bytes of every digit at once (prop_i8.hpp has the order)
+      const int KB = prop_i8::kblocks(n_pad);
+      for (int q = part; q < 4 * KB; q += G) {
+        unsigned w[4][prop_i8::kDigits];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          double v[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const double val = element((q >> 2) * 64 + 16 * i + 4 * (q & 3) + r);
+            rsum += fabs(val);
+            v[r] = val * iscale;
+          }
+          prop_i8::split_digits(v, w[i]);
+        }
+        typedef unsigned u4 __attribute__((ext_vector_type(4)));
+        u4* d = reinterpret_cast<u4*>(Bt) + (size_t)((j >> 4) * KB + (q >> 2)) * prop_i8::kDigits * 64 + (q & 3) * 16 + (j & 15);
+#pragma unroll
+        for (int a = 0; a < prop_i8::kDigits; ++a) d[a * 64] = u4{w[0][a], w[1][a], w[2][a], w[3][a]};
       }
+    }
+    for (int k = part; k < n_pad && !digits; k += G) {
+      const double val = element(k);
       rsum += fabs(val);
       // element (j, k) of the tile-ordered matrix: the part set by k is the
       // same for every lane, so the stores take a uniform base and a fixed
@@ -716,6 +778,7 @@ __device__ void cheb_setup(const ClassDev& c, int t, const ModelAt& mm, double v
   double* cb = c.cheb + (size_t)t * kChebStride;
   const int K = write_cheb(cb, lo, hi, dte, precision, cnt, count_step, c.work);
   if (tid == 0) {
+    cb[CHEB_BSCALE] = bscale;
     if (K < 0) atomicOr(&L.fail, 2);
     if (c.ips) {
       c.ips[(size_t)t * kIpStride + IP_SUB] = 0.0f;

@@ -31,6 +31,7 @@
 // trajectory land on the same XCD and share B in L2.
 
 #include "iesh_internal.hpp"
+#include "prop_i8.hpp"
 #include "prop_ip.hpp"
 
 namespace iesh {
@@ -537,6 +538,30 @@ hipError_t launch_prop(const ClassDev& c, int precision, hipStream_t s) {
   const size_t lds = prop_lds_bytes(c, precision);
   if (precision == IESH_FP64) return launch_prop_t<double, kPropagate>(c, grid, lds, s, nullptr, 0);
   return launch_prop_t<float, kPropagate>(c, grid, lds, s, nullptr, 0);
+}
+
+// FP64 in 8-bit digits.
+size_t i8_b_doubles(int n_pad) { return prop_i8::chosen(n_pad) ? prop_i8::b_doubles(n_pad) : 0; }
+
+hipError_t i8_prepare(ClassDev& c) {
+  if (!prop_i8::chosen(c.md.n_pad)) return hipSuccess;
+  const int n_pad = c.md.n_pad, nr = prop_i8::row_tiles(n_pad), nct = prop_i8::col_tiles(n_pad);
+  c.i8_slabs = ((c.md.N + 7) / 8 + nct - 1) / nct;
+  const void* fn = nr == 1 ? (const void*)prop_i8::k_prop_i8<1, 2>
+                   : nr == 2 ? (const void*)prop_i8::k_prop_i8<2, 2> : (const void*)prop_i8::k_prop_i8<3, 1>;
+  return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)prop_i8::lds_bytes(n_pad));
+}
+
+hipError_t launch_prop_i8(const ClassDev& c, hipStream_t s) {
+  if (c.n_live < 1) return hipSuccess;
+  const dim3 grid((c.n_live + 7) / 8 * 8 * c.i8_slabs), block(64 * prop_i8::kWaves);
+  const size_t lds = prop_i8::lds_bytes(c.md.n_pad);
+  switch (prop_i8::row_tiles(c.md.n_pad)) {
+    case 1: hipLaunchKernelGGL((prop_i8::k_prop_i8<1, 2>), grid, block, lds, s, c); break;
+    case 2: hipLaunchKernelGGL((prop_i8::k_prop_i8<2, 2>), grid, block, lds, s, c); break;
+    default: hipLaunchKernelGGL((prop_i8::k_prop_i8<3, 1>), grid, block, lds, s, c); break;
+  }
+  return hipGetLastError();
 }
 
 // The interaction picture: the 16-column tiles of a trajectory over

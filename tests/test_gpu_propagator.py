@@ -110,3 +110,36 @@ def test_fp64_series_over_orders_and_terms(M, N, dt_factor):
         print(f"M={M} dt x {dt_factor}: |dC| {err:.2e}", flush=True)
         assert err <= 1e-12
     ens.close()
+
+
+# one, two and three row tiles to a wave, full and half last blocks of columns,
+# odd orbital tiles; 48 and 130 take the FP64 instructions
+@pytest.mark.parametrize("M,N", [(48, 9), (100, 8), (111, 41), (120, 60), (130, 20), (144, 24), (200, 100), (207, 17),
+                                 (255, 33), (256, 128), (320, 160), (335, 7)])
+@pytest.mark.parametrize("scale", [0.0, 2.0 ** -60, 2.0 ** 45])
+def test_fp64_orbitals_keep_their_scale(M, N, scale):
+    """The propagation is linear, and everything in it is scaled by powers of
+    two: orbitals times 2^k give the result times 2^k to the bit, whatever the
+    other orbitals' scales, and zero orbitals stay zero.  Against the oracle's
+    exponential within 1e-12 of an orbital's norm."""
+    cfg = make_cfg("c2", M=M, N=N)
+    m = models.from_config(cfg, M=M)
+    states = random_states(m, N, 2, seed=5 + M, xs=[-2.0, 3.0], v_scale=2e-3)
+    ref = [dyn.step(m, s, cfg["dt"], 2.0, dyn.el.forces(m, s.x, s.s))[0].C for s in states]
+    from paper_2212_00518_amd import unpack_C
+    out = []
+    for f in (1.0, scale):
+        ens = ensemble(cfg, 2)
+        for s in states:
+            s.C = s.C.copy()
+            s.C[:, ::3] *= f
+        upload(ens, states)
+        ens.step()
+        C = ens.get_state()[2]
+        out.append([unpack_C(C, t, m.n, N, ens.n_max, ens.N_max) for t in range(2)])
+        ens.close()
+    for t in range(2):
+        assert np.max(np.abs(out[0][t] - ref[t])) <= 1e-12
+        want = out[0][t].copy()
+        want[:, ::3] *= scale
+        assert np.array_equal(out[1][t], want)
