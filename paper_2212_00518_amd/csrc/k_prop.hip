@@ -545,22 +545,16 @@ size_t i8_b_doubles(int n_pad) { return prop_i8::chosen(n_pad) ? prop_i8::b_doub
 
 hipError_t i8_prepare(ClassDev& c) {
   if (!prop_i8::chosen(c.md.n_pad)) return hipSuccess;
-  const int n_pad = c.md.n_pad, nr = prop_i8::row_tiles(n_pad), nct = prop_i8::col_tiles(n_pad);
+  const int nct = prop_i8::shape(c.md.n_pad).nct;
   c.i8_slabs = ((c.md.N + 7) / 8 + nct - 1) / nct;
-  const void* fn = nr == 1 ? (const void*)prop_i8::k_prop_i8<1, 2>
-                   : nr == 2 ? (const void*)prop_i8::k_prop_i8<2, 2> : (const void*)prop_i8::k_prop_i8<3, 1>;
-  return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)prop_i8::lds_bytes(n_pad));
+  return hipFuncSetAttribute((const void*)prop_i8::kernel(c.md.n_pad), hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)prop_i8::lds_bytes(c.md.n_pad));
 }
 
 hipError_t launch_prop_i8(const ClassDev& c, hipStream_t s) {
   if (c.n_live < 1) return hipSuccess;
-  const dim3 grid((c.n_live + 7) / 8 * 8 * c.i8_slabs), block(64 * prop_i8::kWaves);
-  const size_t lds = prop_i8::lds_bytes(c.md.n_pad);
-  switch (prop_i8::row_tiles(c.md.n_pad)) {
-    case 1: hipLaunchKernelGGL((prop_i8::k_prop_i8<1, 2>), grid, block, lds, s, c); break;
-    case 2: hipLaunchKernelGGL((prop_i8::k_prop_i8<2, 2>), grid, block, lds, s, c); break;
-    default: hipLaunchKernelGGL((prop_i8::k_prop_i8<3, 1>), grid, block, lds, s, c); break;
-  }
+  const dim3 grid((c.n_live + 7) / 8 * 8 * c.i8_slabs), block(64 * prop_i8::shape(c.md.n_pad).waves);
+  hipLaunchKernelGGL(prop_i8::kernel(c.md.n_pad), grid, block, prop_i8::lds_bytes(c.md.n_pad), s, c);
   return hipGetLastError();
 }
 

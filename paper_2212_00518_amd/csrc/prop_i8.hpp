@@ -18,8 +18,8 @@
 // twice that).  At M = 200 a product takes 17 pairs of digits on average, and
 // the integer instructions do 64 for the time of one FP64 product.
 //
-// A work-group of eight waves takes NCT tiles of 16 columns (8 orbitals as
-// [Re of 8 | Im of 8]); wave w has the row tiles w, w + 8, ..  The digits of b
+// A work-group of W waves takes NCT tiles of 16 columns (8 orbitals as
+// [Re of 8 | Im of 8]); wave w has the row tiles w, w + W, ..  The digits of b
 // pass through LDS (two buffers, one barrier a term) in the operand's order:
 // row tile 4 kb + t, lane group g and accumulator row r are byte 4 t + r of
 // lane 16 g + column.  The digits of B come from memory in that order, each
@@ -27,7 +27,8 @@
 //
 // At M = 200 the matrix instructions are busy for a third of the time and the
 // vector ones (digits, levels, recurrence: 235 to a tile and term) for another;
-// the registers allow two waves to a SIMD, which the barrier keeps in step.
+// the registers allow two waves to a SIMD, and the barrier keeps those of one
+// work-group in step.
 // One FP64 propagation of saturating batches, ms, FP64 instructions / this:
 // 2048 trajectories of M = 200 9.3 / 6.8, 512 of M = 120 0.56 / 0.37, 256 of
 // M = 320 4.9 / 2.5; of 16 trajectories of M = 100 0.098 / 0.046.
@@ -44,7 +45,6 @@ typedef int i4 __attribute__((ext_vector_type(4)));
 typedef double d2 __attribute__((ext_vector_type(2)));
 
 constexpr int kDigits = 7;
-constexpr int kWaves = 8;
 constexpr int kBits = 60;
 __host__ __device__ constexpr int kblocks(int n_pad) { return (n_pad + 63) / 64; }
 __host__ __device__ constexpr size_t b_doubles(int n_pad) { return (size_t)n_pad / 16 * kblocks(n_pad) * kDigits * 128; }
@@ -162,8 +162,8 @@ __device__ __forceinline__ void product(const unsigned char* Arow, const unsigne
     }
 }
 
-template <int NR, int NCT>
-__global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_prop_i8(ClassDev c) {
+template <int W, int NR, int NCT>
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_prop_i8(ClassDev c) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int n_pad = c.md.n_pad, RT = n_pad >> 4, KB = kblocks(n_pad), N = c.md.N;
   const bool half = (RT & 3) == 1 || (RT & 3) == 2;
@@ -181,7 +181,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
   const double* cb = c.cheb + (size_t)t * kChebStride;
   const int K = (int)cb[CHEB_K];
   const double invr = cb[CHEB_INVR], cc = cb[CHEB_C], bscale = cb[CHEB_BSCALE];
-  for (int i = tid; i < n_pad; i += 64 * kWaves) lam[i] = c.lam_mid[(size_t)t * n_pad + i] - cc;
+  for (int i = tid; i < n_pad; i += 64 * W) lam[i] = c.lam_mid[(size_t)t * n_pad + i] - cc;
 
   // X: rows 16 rt + 4 g + r of the lane's column; a lane reads two complex
   // rows, the lane of the orbital's other part has the two others
@@ -193,7 +193,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
     const double* Cg = c.C64 + ((size_t)t * N + (o < N ? o : 0)) * n_pad * 2 + (4 * g + (is_re ? 0 : 2)) * 2;
 #pragma unroll
     for (int i = 0; i < NR; ++i) {
-      const int rt = wave + kWaves * i;
+      const int rt = wave + W * i;
       const bool in = rt < RT && o < N;
       const d2* p = reinterpret_cast<const d2*>(Cg + (rt < RT ? rt : 0) * 32);
       const d2 v0 = p[0], v1 = p[1];
@@ -219,7 +219,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
 #pragma unroll
   for (int ct = 0; ct < NCT; ++ct) {
     double s = 0.0;
-    for (int w = 0; w < kWaves; ++w) s += part[(w * NCT + ct) * 16 + col];
+    for (int w = 0; w < W; ++w) s += part[(w * NCT + ct) * 16 + col];
     int ex = 0;
     (void)frexp(sqrt(s), &ex);
     sx[ct] = s > 0.0 ? ldexp(1.0, ex) : 1.0;
@@ -227,7 +227,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
     if (!(s <= 0x1.fffffffffffffp1023)) sx[ct] = s - s;  // not a number, as the result then is
   }
   __syncthreads();
-  for (int i = tid; i < buf_bytes / 8; i += 64 * kWaves) reinterpret_cast<i4*>(smem)[i] = i4{0, 0, 0, 0};
+  for (int i = tid; i < buf_bytes / 8; i += 64 * W) reinterpret_cast<i4*>(smem)[i] = i4{0, 0, 0, 0};
   __syncthreads();
 
   // lane k: exponent of the bound on b_k of a unit orbital, sum_{m >= k}
@@ -252,7 +252,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
   // digits of b1 = b_m into a buffer
   auto put_digits = [&](int i, int m, unsigned char* dig) {
     const double sb = ldexp(1.0, -__builtin_amdgcn_readlane(eb, m));
-    const int S = __builtin_amdgcn_readlane(lv, m), rt = wave + kWaves * i;
+    const int S = __builtin_amdgcn_readlane(lv, m), rt = wave + W * i;
 #pragma unroll
       for (int ct = 0; ct < NCT; ++ct) {
         const double sc = sb * isx[ct];
@@ -287,7 +287,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
   }
 #pragma unroll
   for (int i = 0; i < NR; ++i)
-    if (wave + kWaves * i < RT) put_digits(i, K, smem);
+    if (wave + W * i < RT) put_digits(i, K, smem);
   __syncthreads();
   for (int k = K - 1; k >= 0; --k) {
     unsigned char* cur = smem + ((K - 1 - k) & 1) * buf_bytes;
@@ -298,7 +298,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
     const double scale = (k == 0 ? 1.0 : 2.0) * invr;
 #pragma unroll
     for (int i = 0; i < NR; ++i) {
-      const int rt = wave + kWaves * i;
+      const int rt = wave + W * i;
       if (rt >= RT) continue;
       double y[NCT][4];
       const unsigned char* Arow = Bg + (size_t)rt * KB * kDigits * 1024;
@@ -333,7 +333,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
   double* rn = c.rown + ((size_t)t * ((N + 7) >> 3) + slab) * n_pad;
 #pragma unroll
   for (int i = 0; i < NR; ++i) {
-    const int rt = wave + kWaves * i;
+    const int rt = wave + W * i;
     if (rt >= RT) continue;
     double s[4] = {};
 #pragma unroll
@@ -360,15 +360,31 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
 
 // Classes that propagate this way: from 7 row tiles on, where the products
 // outweigh the rest.  Saturating batches, ms, FP64 instructions / digits: 5
-// row tiles 0.14 / 0.18, 6 0.25 / 0.26, 7 1.56 / 1.46, 8 0.56 / 0.37, 10 1.04 /
-// 0.87.  Not at 9, where one of the eight waves has two of them (0.76 / 0.87).
-inline bool chosen(int n_pad) { return n_pad / 16 >= 7 && n_pad / 16 != 9; }
+// row tiles 0.14 / 0.18, 6 0.25 / 0.26, 7 1.56 / 1.47, 8 0.56 / 0.37, 9 0.76 /
+// 0.65, 10 1.04 / 0.76; of 16 trajectories at 7 to 9 half the time.
+inline bool chosen(int n_pad) { return n_pad / 16 >= 7; }
 
-// Row tiles to a wave, and orbital tiles to a work-group (what its registers hold).
-inline int row_tiles(int n_pad) { return (n_pad / 16 + kWaves - 1) / kWaves; }
-inline int col_tiles(int n_pad) { return row_tiles(n_pad) < 3 ? 2 : 1; }
+// Waves of a work-group, row tiles to a wave and orbital tiles to a work-group,
+// as many as the registers of two waves to a SIMD hold.  Two orbital tiles
+// share the loads of B; at 9 to 12 row tiles two work-groups of four waves with
+// one each, whose phases overlap, are faster all the same (10 row tiles 0.76
+// against 0.87 ms, 11 0.90 against 1.07), at 13 to 16 they spill (13: 7.2
+// against 6.8), at 8 they only load more (0.40 against 0.37).
+struct Shape {
+  int waves, nr, nct;
+};
+inline Shape shape(int n_pad) {
+  const int rt = n_pad / 16;
+  return rt <= 8 ? Shape{8, 1, 2} : rt <= 12 ? Shape{4, 3, 1} : rt <= 16 ? Shape{8, 2, 2} : Shape{8, 3, 1};
+}
 inline size_t lds_bytes(int n_pad) {
-  return (size_t)2 * col_tiles(n_pad) * kDigits * kblocks(n_pad) * 1024 + sizeof(double) * n_pad;
+  return (size_t)2 * shape(n_pad).nct * kDigits * kblocks(n_pad) * 1024 + sizeof(double) * n_pad;
+}
+
+typedef void (*Kernel)(ClassDev);
+inline Kernel kernel(int n_pad) {
+  const Shape s = shape(n_pad);
+  return s.nr == 1 ? k_prop_i8<8, 1, 2> : s.nr == 2 ? k_prop_i8<8, 2, 2> : s.waves == 4 ? k_prop_i8<4, 3, 1> : k_prop_i8<8, 3, 1>;
 }
 
 }  // namespace prop_i8

@@ -113,7 +113,7 @@ def test_fp64_series_over_orders_and_terms(M, N, dt_factor):
 
 
 # one, two and three row tiles to a wave, full and half last blocks of columns,
-# odd orbital tiles; 48 and 130 take the FP64 instructions
+# odd orbital tiles, four and eight waves; 48 takes the FP64 instructions
 @pytest.mark.parametrize("M,N", [(48, 9), (100, 8), (111, 41), (120, 60), (130, 20), (144, 24), (200, 100), (207, 17),
                                  (255, 33), (256, 128), (320, 160), (335, 7)])
 @pytest.mark.parametrize("scale", [0.0, 2.0 ** -60, 2.0 ** 45])
