@@ -184,9 +184,12 @@ __device__ inline void arrive(int n) {
 // y = (e^{-M} - 1) w0 and T2 from e^{iL} (w0 + y), x <- E_post (u + d),
 // d = y + Z (T1 + T2).  The small parts stay out of u until the last
 // rounding: added one by one to numbers of 24 bits, whatever is below half
-// a unit would be lost in every step the same way (at M = 44 with two
-// sub-steps the orbitals were 1.6e-6 off after 99 steps that way, 0.7e-6
-// with the Chebyshev series).
+// a unit would be lost in every step the same way.  For the same reason the
+// cosine's term of a phase is added last: the phase of a state near the Fermi
+// level is small, its cosine's term nearly the whole number, and rounded
+// before the sine's it is off by the same amount step after step (M = 106,
+// Gauss-Legendre bath, two sub-steps, 99 steps: orbitals 8.8e-7 off,
+// 6.2e-7 with the Chebyshev series, 4.1e-7 this way).
 template <int RT, int R>
 __device__ inline void sub_intervals(const Group& gr, float (&x)[RT][4]) {
   constexpr int n_pad = 16 * RT;
@@ -220,7 +223,7 @@ __device__ inline void sub_intervals(const Group& gr, float (&x)[RT][4]) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const float xr = x[rt][r], xp = sg * swap8(xr);
-        x[rt][r] = fmaf(c[1][r], xp, fmaf(c[0][r], xr, fmaf(c[3][r], xp, c[2][r] * xr)));
+        x[rt][r] = fmaf(c[0][r], xr, fmaf(c[1][r], xp, fmaf(c[3][r], xp, c[2][r] * xr)));
         m = fmaxf(m, fabsf(x[rt][r]));
       }
       each_column<R>(zp, n_pad, rt * 16 + 4 * g, [&](int f, f4 z) {
@@ -399,7 +402,7 @@ __device__ inline void sub_intervals(const Group& gr, float (&x)[RT][4]) {
       for (int r = 0; r < 4; ++r) {
         const float xr = x[rt][r] * ux, xp = sg * swap8(xr), dr = dv[r], dp = sg * swap8(dr);
         const float low = fmaf(c[1][r], dp, fmaf(c[0][r], dr, fmaf(c[3][r], xp, c[2][r] * xr)));
-        x[rt][r] = fmaf(c[1][r], xp, fmaf(c[0][r], xr, low));
+        x[rt][r] = fmaf(c[0][r], xr, fmaf(c[1][r], xp, low));
       }
       if (rt & 1) tile_end();
     }

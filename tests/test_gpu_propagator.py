@@ -143,3 +143,33 @@ def test_fp64_orbitals_keep_their_scale(M, N, scale):
         want = out[0][t].copy()
         want[:, ::3] *= scale
         assert np.array_equal(out[1][t], want)
+
+
+@pytest.mark.parametrize("M,N", [(44, 25), (106, 53)])
+def test_mixed_phases_round_independently(M, N):
+    """Thermal orbitals on a Gauss-Legendre bath, whose levels crowd at the
+    Fermi level, where the phase of a sub-step is small.  A propagation takes
+    two rotations of at most two roundings each, and both parts of a number of
+    modulus at most one round: were the roundings independent (uniform within
+    2^-25), the error after n propagations would be sqrt(8 n) 2^-25 / sqrt(3).
+    A rounding that repeats itself step after step exceeds that."""
+    cfg = make_cfg("c2gl", M=M, N=N)
+    T, steps, sub = 48, 99, 2
+    rs = np.random.default_rng(M)
+    mass, omega, kT = cfg["model"]["mass"], cfg["model"]["omega"], cfg["kT"]
+    x = rs.normal(0.0, np.sqrt(kT / (mass * omega ** 2)), T)
+    v = rs.normal(0.0, np.sqrt(kT / mass), T)
+    out = []
+    for precision in ("fp64", "mixed"):
+        ens = ensemble(cfg, T, precision=precision, elec_substeps=sub, lowdin_every=0)
+        ens.init_thermal(x, v)
+        ens.run(steps)
+        out.append(ens.get_state())
+        ens.close()
+    same = np.all(out[0][3] == out[1][3], axis=1) & (np.abs(out[0][0] - out[1][0]) < 1e-9)  # the same hops
+    assert np.sum(same) >= 40
+    C64, C32 = (o[2].reshape(T, -1)[same] for o in out)
+    err = np.linalg.norm(C32 - C64, axis=1) / np.linalg.norm(C64, axis=1)
+    rms = np.sqrt(np.mean(err ** 2))
+    print(f"M={M}: rms relative error {rms:.2e}", flush=True)
+    assert rms <= np.sqrt(8.0 * steps * sub) * 2.0 ** -25 / np.sqrt(3.0)
