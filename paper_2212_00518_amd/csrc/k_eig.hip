@@ -811,11 +811,16 @@ __device__ void cheb_setup(const ClassDev& c, int t, const ModelAt& mm, double v
 // its weighted error; their sum may reach one FP32 rounding unit (2^-24; the
 // measured truncation is a fifth of the sum or less), the Taylor tail 2^-27.
 // A trajectory that needs more than three sub-intervals takes the Chebyshev
-// series.
+// series, and so does one for which the series might need more than its most
+// terms: whether such a step is refused is the series' to say.
 constexpr double kIpTol = 0x1p-24;
 constexpr double kIpTaylorTol = 0x1p-27;
 constexpr int kIpMaxSub = 3;
 constexpr int kIpMaxTerms = 8;
+// The FP32 series has its 62 terms up to rho = 35.9 (radius of A's Gershgorin
+// interval times the step).  The row sums that widen the interval past the
+// eigenvalues of Lambda are at most sqrt(n) ||B||.
+constexpr double kIpMaxRho = 35.0;
 // positive nodes and weights of the two- and four-point Gauss rules for
 // 1 - u^2 on [-1, 1]: sqrt(1/5); sqrt((7 -+ 2 sqrt 7) / 21), weights
 // (14 +- sqrt 7)/30 (1 - u^2)
@@ -883,6 +888,7 @@ __device__ bool ip_setup(const ClassDev& c, int t, const ModelAt& mm, double vfa
   const double vn = sqrt(red[2]);
   const double bn = 1.3154 * 3.14159265358979324 * (fabs(a) * red[0] + 2.0 * fabs(b) * sqrt(red[0] * red[1]));
   const double nn = fabs(a) + 2.0 * fabs(b) * vn;
+  if (!((0.5 * (L.lam[n - 1] - L.lam[0]) + sqrt((double)n) * bn) * dte <= kIpMaxRho)) return false;
   int sub = 0, pairs = 1;
 #pragma unroll
   for (int s = 1; s <= kIpMaxSub; ++s)

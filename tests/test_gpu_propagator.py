@@ -173,3 +173,26 @@ def test_mixed_phases_round_independently(M, N):
     rms = np.sqrt(np.mean(err ** 2))
     print(f"M={M}: rms relative error {rms:.2e}", flush=True)
     assert rms <= np.sqrt(8.0 * steps * sub) * 2.0 ** -25 / np.sqrt(3.0)
+
+
+# half the 64 eV band times the step: 31.8, 36.5 and 47; the FP32 series has
+# its 62 terms up to 35.9 and refuses a longer step
+@pytest.mark.parametrize("M,N", [(40, 20), (160, 80)])
+@pytest.mark.parametrize("dt,accepted", [(27.0, True), (31.0, False), (40.0, False)])
+def test_steps_beyond_the_series_stay_refused(M, N, dt, accepted):
+    """Trajectories at rest and slow ones, whose propagator the interaction
+    picture needs no series for, are refused with the others."""
+    from paper_2212_00518_amd import _lib
+    cfg = make_cfg("c3", M=M, N=N)
+    cfg["dt"] = dt
+    m = models.from_config(cfg, M=M)
+    T = 4
+    states = random_states(m, N, T, seed=M, xs=np.linspace(4.0, 8.0, T), v_scale=0.0)
+    for t, s in enumerate(states):
+        s.v[0] = -1e-6 * t
+    ens = ensemble(cfg, T, precision="mixed", lowdin_every=0)
+    upload(ens, states)
+    ens.step()
+    status = ens.status()
+    ens.close()
+    assert np.all(status == (0 if accepted else _lib.TRAJ_NONCONV)), status
