@@ -167,10 +167,12 @@ void choose_slabs(ClassDev& c, int precision) { set_slabs(c, widest_slab(c, prec
 int autotune_slabs(iesh_ctx* ctx, ClassDev& c) {
   const int prec = ctx->run.precision;
   const int widest = widest_slab(c, prec, 1 << 20);
-  // interaction-picture classes run this kernel for a few queued
-  // trajectories only: one-tile slabs spread those over the most work-groups
+  // interaction-picture classes run this kernel over a queue, in slabs of one
+  // tile while it is short.  For a long one their own width follows what the
+  // timing below picks for saturating batches of FP32: one tile from 9 row
+  // tiles on, two or three below.
   if (c.ips) {
-    set_slabs(c, 1);
+    set_slabs(c, c.md.n_pad >= 9 * 16 ? 1 : std::min(widest, 3));
     return prop_prepare(c, prec) == hipSuccess ? IESH_OK : fail(ctx, IESH_EDEVICE, "propagation LDS attribute");
   }
   if (widest <= 1 || c.n_traj < 64) {
@@ -1033,11 +1035,11 @@ int iesh_create(const iesh_model_desc* models, int32_t n_models, const int32_t* 
         c.b_stride = std::max(c.b_stride, (size_t)n_pad * 32 * ip_kblocks(n_pad));
         if ((rc = dalloc(ctx, &c.ips, (size_t)T * kIpStride)) ||
             (rc = dalloc(ctx, &c.ipv, (size_t)T * kIpPlanes * n_pad)) ||
-            (rc = dalloc(ctx, &c.chebq, (size_t)2 + T)))
+            (rc = dalloc(ctx, &c.chebq, (size_t)CHEBQ_LIST + T)))
           return bail(rc);
         if (ip_prepare(c) != hipSuccess)
           return (fail(ctx, IESH_EDEVICE, "propagation LDS attribute"), bail(IESH_EDEVICE));
-        c.cheb_groups = 4 * ctx->n_cu;
+        c.cheb_groups = (4 * ctx->n_cu + 7) / 8 * 8;
       }
       if ((rc = dalloc(ctx, &c.Bt32, (size_t)T * c.b_stride)) ||
           (rc = dalloc(ctx, &c.low, lowdin_scratch_elems(c))) ||

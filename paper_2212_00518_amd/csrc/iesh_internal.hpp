@@ -47,7 +47,7 @@ enum ChebSlot { CHEB_C = 0, CHEB_INVR = 1, CHEB_K = 2, CHEB_RHO = 3, CHEB_BSCALE
 // Interaction-picture propagation of the mixed path (k_eig.hip sets it up,
 // prop_ip.hpp applies it).  Per trajectory ips[] holds IP_SUB sub-intervals
 // (0: the trajectory takes the Chebyshev series of cheb[] instead), IP_TERMS
-// Taylor terms, IP_RANK columns of Z, IP_UNSCALE = 1/scale of the stored M,
+// Taylor terms (the series: slabs the trajectory was propagated in), IP_RANK columns of Z, IP_UNSCALE = 1/scale of the stored M,
 // then the R x R matrices D and -D (Z^T Z) D / 2; ipv[] holds planes of n_pad
 // floats: cos and sin of the phases before and after a sub-interval (each as
 // two floats, high and low part), and the columns of Z.
@@ -56,6 +56,9 @@ enum IpSlot { IP_SUB = 0, IP_TERMS = 1, IP_RANK = 2, IP_UNSCALE = 3, IP_D = 8, I
 constexpr int kIpStride = 8 + 2 * 64;
 enum IpPlane { IPV_PRE = 0, IPV_POST = 4, IPV_Z = 8 };
 constexpr int kIpPlanes = 8 + kIpMaxRank;
+// Layout of chebq[]: trajectories queued, work-groups done, items taken beyond
+// the first of every work-group by XCD, the list.
+enum ChebqSlot { CHEBQ_COUNT = 0, CHEBQ_DONE = 1, CHEBQ_NEXT = 2, CHEBQ_LIST = 10 };
 // k-blocks of 32 columns in the stored M (f16 pairs, see prop_ip.hpp)
 __host__ __device__ constexpr int ip_kblocks(int n_pad) { return (n_pad + 31) / 32; }
 
@@ -140,9 +143,9 @@ struct ClassDev {
   // interaction-picture propagation (mixed arrowhead classes, else nullptr)
   float* ips = nullptr;     // [T][kIpStride]
   float* ipv = nullptr;     // [T][kIpPlanes][n_pad]
-  int32_t* chebq = nullptr; // [2 + T] queue of the trajectories that take the Chebyshev
-                            // series this step: count, work-groups done, list
-  int cheb_groups = 0;      // most work-groups of the launch over that queue
+  int32_t* chebq = nullptr; // [CHEBQ_LIST + T] queue of the trajectories that take the
+                            // Chebyshev series this step
+  int cheb_groups = 0;      // most work-groups of the launch over that queue (a multiple of 8)
   int ip_groups = 0;        // interaction-picture work-groups per trajectory
   int ip_waves = 0;         // waves of each (a 16-column tile a wave)
   double* gbuf = nullptr;   // [T][N][n_pad] hop probabilities (query mode)

@@ -782,7 +782,7 @@ __device__ void cheb_setup(const ClassDev& c, int t, const ModelAt& mm, double v
     if (K < 0) atomicOr(&L.fail, 2);
     if (c.ips) {
       c.ips[(size_t)t * kIpStride + IP_SUB] = 0.0f;
-      c.chebq[2 + atomicAdd(&c.chebq[0], 1)] = t;
+      c.chebq[CHEBQ_LIST + atomicAdd(&c.chebq[CHEBQ_COUNT], 1)] = t;
     }
   }
 }

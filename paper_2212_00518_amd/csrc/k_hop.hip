@@ -1273,7 +1273,8 @@ __device__ void filter_one(const ClassDev& c, int t, double dt_run, uint64_t see
   const size_t base = (size_t)t * N * n_pad;
   double fro_part = 0.0;
   const int slabs_max = (N + 7) >> 3;
-  const int n_slabs = c.ips && c.ips[(size_t)t * kIpStride + IP_SUB] != 0.0f ? slabs_max
+  const float* ips = c.ips ? c.ips + (size_t)t * kIpStride : nullptr;
+  const int n_slabs = ips ? (ips[IP_SUB] != 0.0f ? slabs_max : (int)ips[IP_TERMS])
                       : c.i8_slabs ? c.i8_slabs : c.n_slabs;
   for (int b = tid; b < n_pad; b += kFltThreads) {
     double s2 = 0.0;

@@ -196,3 +196,46 @@ def test_steps_beyond_the_series_stay_refused(M, N, dt, accepted):
     status = ens.status()
     ens.close()
     assert np.all(status == (0 if accepted else _lib.TRAJ_NONCONV)), status
+
+
+# more items than work-groups, in slabs of three tiles and of one, of the first
+# and the second register tier, and fewer; the queue is filled anew by every
+# sub-step
+@pytest.mark.parametrize("substeps", [1, 2])
+@pytest.mark.parametrize("name,M,N,T", [("c3", 40, 20, 1500), ("c2", 100, 50, 300), ("c3", 160, 80, 160),
+                                        ("c2", 260, 40, 320), ("c2", 100, 50, 24)])
+def test_long_queues_of_the_series(name, M, N, T, substeps):
+    """Ensembles of which two thirds are too fast for the interaction picture,
+    over three steps: a sample against the oracle (the Chebyshev series' 4e-6
+    for each of its up to six propagations), and all states bit by bit with and
+    without the no-hop bound, which reads the row norms by slab."""
+    cfg = make_cfg(name, M=M, N=N)
+    m = models.from_config(cfg, M=M)
+    steps = 3
+    rs = np.random.default_rng(M + T)
+    x = rs.uniform(4.0, 9.0, T)
+    v = np.where(np.arange(T) % 3 == 0, 0.0, (0.1 if name == "c3" else 0.03) * rs.choice([-1.0, 1.0], T))
+    C = np.stack([random_states(m, N, 1, seed=q, xs=[0.0], v_scale=0.0)[0].C for q in range(8)])
+    states = [dyn.State([x[t]], [v[t]], C[t % 8], np.arange(N)) for t in range(T)]
+    out = []
+    for off in (0, 1):
+        ens = ensemble(cfg, T, precision="mixed", elec_substeps=substeps, lowdin_every=0, hop_filter_off=off)
+        upload(ens, states)
+        ens.run(steps)
+        out.append(ens.get_state())
+        assert np.all(ens.status() == 0)
+        terms = ens.work()[0] / (T * steps * substeps)
+        ens.close()
+    assert all(np.array_equal(a, b) for a, b in zip(*out))
+    print(f"products per propagation {terms:.1f}", flush=True)
+    assert terms > 5.0  # a plan takes at most four at rest
+    from paper_2212_00518_amd import unpack_C
+    ok = 0
+    for t in np.unique(np.linspace(0, T - 1, 12).astype(int)):
+        ref, _, _ = dyn.run(m, states[t], cfg["dt"], steps, cfg["seed"], int(t), substeps=substeps)
+        if not np.array_equal(out[0][3][t][:N], ref.s):
+            continue  # another hop
+        err = np.max(np.abs(unpack_C(out[0][2], t, m.n, N, m.n, N) - ref.C))
+        assert err <= 4e-6 * steps * substeps, (t, err)
+        ok += 1
+    assert ok >= 6
