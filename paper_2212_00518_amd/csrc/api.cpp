@@ -616,10 +616,9 @@ int enqueue_step(iesh_ctx* ctx, int record) {
     for (auto& c : ctx->cls)
       if (c.n_traj)
         HIPTRY(ctx, timed(ctx, IESH_TIMER_PROP, [&] {
-                 if (c.i8_slabs) return launch_prop_i8(c, s);
-                 if (!c.ips) return launch_prop(c, r.precision, s);
-                 const hipError_t e = launch_prop_ip(c, s);
-                 return e == hipSuccess ? launch_prop_queue(c, s) : e;
+                 if (!c.i8_slabs && !c.ips) return launch_prop(c, r.precision, s);
+                 const hipError_t e = c.ips ? launch_prop_ip(c, s) : launch_prop_i8(c, s);
+                 return e == hipSuccess ? launch_prop_queue(c, r.precision, s) : e;
                }));
     return IESH_OK;
   };
@@ -1034,17 +1033,19 @@ int iesh_create(const iesh_model_desc* models, int32_t n_models, const int32_t* 
         // the interaction picture's M (f16 pairs) shares the buffer of B
         c.b_stride = std::max(c.b_stride, (size_t)n_pad * 32 * ip_kblocks(n_pad));
         if ((rc = dalloc(ctx, &c.ips, (size_t)T * kIpStride)) ||
-            (rc = dalloc(ctx, &c.ipv, (size_t)T * kIpPlanes * n_pad)) ||
-            (rc = dalloc(ctx, &c.chebq, (size_t)CHEBQ_LIST + T)))
+            (rc = dalloc(ctx, &c.ipv, (size_t)T * kIpPlanes * n_pad)))
           return bail(rc);
         if (ip_prepare(c) != hipSuccess)
           return (fail(ctx, IESH_EDEVICE, "propagation LDS attribute"), bail(IESH_EDEVICE));
-        c.cheb_groups = (4 * ctx->n_cu + 7) / 8 * 8;
       }
       if ((rc = dalloc(ctx, &c.Bt32, (size_t)T * c.b_stride)) ||
           (rc = dalloc(ctx, &c.low, lowdin_scratch_elems(c))) ||
           (rc = dalloc(ctx, &c.defect, (size_t)T)))
         return bail(rc);
+    }
+    if (c.ips || c.i8_slabs) {
+      if ((rc = dalloc(ctx, &c.chebq, (size_t)CHEBQ_LIST + 2 * T))) return bail(rc);
+      c.cheb_groups = (4 * ctx->n_cu + 7) / 8 * 8;
     }
     if (hipError_t e = prop_prepare(c, r.precision); e != hipSuccess)
       return (fail(ctx, IESH_EDEVICE, std::string("propagation LDS attribute: ") +

@@ -40,14 +40,14 @@ enum GeoSlot {
 };
 
 // Chebyshev parameter block (layout of cheb[]): [0] centre c, [1] 1/radius,
-// [2] number of terms K (as double), [3] radius*dt, then K complex
-// coefficients (re, im) starting at [8].
+// [2] number of terms K (as double), [3] radius*dt, [4] scale of B in 8-bit
+// digits (0: B as it is), then K complex coefficients (re, im) starting at [8].
 enum ChebSlot { CHEB_C = 0, CHEB_INVR = 1, CHEB_K = 2, CHEB_RHO = 3, CHEB_BSCALE = 4, CHEB_COEF = 8 };
 
 // Interaction-picture propagation of the mixed path (k_eig.hip sets it up,
 // prop_ip.hpp applies it).  Per trajectory ips[] holds IP_SUB sub-intervals
 // (0: the trajectory takes the Chebyshev series of cheb[] instead), IP_TERMS
-// Taylor terms (the series: slabs the trajectory was propagated in), IP_RANK columns of Z, IP_UNSCALE = 1/scale of the stored M,
+// Taylor terms, IP_RANK columns of Z, IP_UNSCALE = 1/scale of the stored M,
 // then the R x R matrices D and -D (Z^T Z) D / 2; ipv[] holds planes of n_pad
 // floats: cos and sin of the phases before and after a sub-interval (each as
 // two floats, high and low part), and the columns of Z.
@@ -57,7 +57,8 @@ constexpr int kIpStride = 8 + 2 * 64;
 enum IpPlane { IPV_PRE = 0, IPV_POST = 4, IPV_Z = 8 };
 constexpr int kIpPlanes = 8 + kIpMaxRank;
 // Layout of chebq[]: trajectories queued, work-groups done, items taken beyond
-// the first of every work-group by XCD, the list.
+// the first of every work-group by XCD, the list [T], and by trajectory the
+// slabs it was propagated in when it was last queued [T].
 enum ChebqSlot { CHEBQ_COUNT = 0, CHEBQ_DONE = 1, CHEBQ_NEXT = 2, CHEBQ_LIST = 10 };
 // k-blocks of 32 columns in the stored M (f16 pairs, see prop_ip.hpp)
 __host__ __device__ constexpr int ip_kblocks(int n_pad) { return (n_pad + 31) / 32; }
@@ -104,7 +105,8 @@ struct ClassDev {
   int traj_offset;      // first global trajectory index of this class
   int nct_max;          // column tiles per propagation work-group
   int n_slabs;          // propagation work-groups per trajectory
-  int i8_slabs = 0;     // the same of the FP64 propagation in 8-bit digits (0: the class does not use it)
+  int i8_slabs = 0;     // the same of the FP64 propagation in 8-bit digits (0: the class does not use it);
+                        // n_slabs then holds for its queue and for prescribed paths
   // [T][ceil(N / 8)][n_pad]: for propagation slab s of trajectory t, the
   // squared norms over the slab's orbitals of every row of C after the last
   // propagation (sum_j |C[i][j]|^2), read by the no-hop bound
@@ -143,8 +145,8 @@ struct ClassDev {
   // interaction-picture propagation (mixed arrowhead classes, else nullptr)
   float* ips = nullptr;     // [T][kIpStride]
   float* ipv = nullptr;     // [T][kIpPlanes][n_pad]
-  int32_t* chebq = nullptr; // [CHEBQ_LIST + T] queue of the trajectories that take the
-                            // Chebyshev series this step
+  int32_t* chebq = nullptr; // [CHEBQ_LIST + 2 T] (these classes and those with i8_slabs) queue of
+                            // the trajectories that k_prop_queue takes this step
   int cheb_groups = 0;      // most work-groups of the launch over that queue (a multiple of 8)
   int ip_groups = 0;        // interaction-picture work-groups per trajectory
   int ip_waves = 0;         // waves of each (a 16-column tile a wave)
@@ -374,10 +376,11 @@ hipError_t launch_dense_init_thermal(const ClassDev& c, double kT, uint64_t seed
 hipError_t launch_prop(const ClassDev& c, int precision, hipStream_t s);
 // interaction-picture propagation (prop_ip.hpp): ip_prepare picks the launch
 // shape of a class and reserves its LDS; launch_prop_queue (k_prop.hip) takes
-// the trajectories left to the Chebyshev series
+// the trajectories left to the Chebyshev series, on the FP64 path those left to
+// the FP64 instructions
 hipError_t ip_prepare(ClassDev& c);
 hipError_t launch_prop_ip(const ClassDev& c, hipStream_t s);
-hipError_t launch_prop_queue(const ClassDev& c, hipStream_t s);
+hipError_t launch_prop_queue(const ClassDev& c, int precision, hipStream_t s);
 hipError_t launch_prop_taps(const ClassDev& c, int mode, double* taps, int tap_k, hipStream_t s);
 int prop_max_col_tiles(int precision);
 int hop_resident_groups(const ClassDev& c, int precision, int n_cu);

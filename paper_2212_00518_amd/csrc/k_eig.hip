@@ -639,6 +639,11 @@ __device__ void load_bath(const ClassDev& c, EigLds& L) {
   __syncthreads();
 }
 
+// Montgomery and Vaughan's inequality for sum x_j x_k / (lambda_j - lambda_k)
+// with the gaps to the nearest neighbours: ||B|| is at most this constant
+// (Preissmann's) times the bound on its elements below.
+constexpr double kHilbert = 1.3154 * 3.14159265358979324;
+
 // Propagator of one trajectory as a Chebyshev series: the coupling matrix
 // B = vD in the propagation kernel's tile order, the Gershgorin interval of
 // A = diag(lambda) - iB and the series' coefficients.  mm holds the model at
@@ -654,10 +659,12 @@ __device__ void cheb_setup(const ClassDev& c, int t, const ModelAt& mm, double v
   for (int k = tid; k < n; k += kEigThreads) L.eo[k] = L.e[L.org[k]];
   __syncthreads();
   // the FP64 classes' B in 8-bit digits (not along prescribed paths, whose
-  // other products take B itself): scaled by a power of two above every
+  // other products take B itself): scaled by a power of two by a bound on every
   // element, |B_jk| <= |a| m1 + 2 |b| sqrt(m1 m2) with the maxima of q0^2 and
-  // (q0 mu)^2 over the gap to the nearest neighbour
-  const bool digits = c.i8_slabs && !c.path;
+  // (q0 mu)^2 over the gap to the nearest neighbour.  Where the series asks more
+  // of the digits than they hold (prop_i8.hpp), B is written as it is and the
+  // trajectory queued.
+  bool digits = c.i8_slabs && !c.path;
   double bscale = 1.0, iscale = 1.0;
   if (digits) {
     double m1 = 0.0, m2 = 0.0;
@@ -685,11 +692,14 @@ __device__ void cheb_setup(const ClassDev& c, int t, const ModelAt& mm, double v
       m2 = fmax(m2, __shfl_xor(m2, sh));
     }
     __syncthreads();
-    int ex = 0;
-    (void)frexp(fabs(vfac * mm.dh) * m1 + 2.0 * fabs(vfac * mm.rho) * sqrt(m1 * m2), &ex);
-    ex = min(max(ex, -900), 900);
+    const double most = fabs(vfac * mm.dh) * m1 + 2.0 * fabs(vfac * mm.rho) * sqrt(m1 * m2);
+    const int ex = min(max(prop_i8::scale_exponent(most), -900), 900);
     bscale = ldexp(1.0, ex);
     iscale = ldexp(1.0, -ex);
+    // the radius of A's interval is at least that of Lambda's, and at most that
+    // and sqrt(n) ||B|| (kIpMaxRho)
+    const double r = 0.5 * (L.lam[n - 1] - L.lam[0]);
+    digits = prop_i8::holds(bscale, r, (r + sqrt((double)n) * kHilbert * most) * dte);
   }
   // small orders: a row's columns are dealt to G threads
   int G = 1;
@@ -778,12 +788,10 @@ __device__ void cheb_setup(const ClassDev& c, int t, const ModelAt& mm, double v
   double* cb = c.cheb + (size_t)t * kChebStride;
   const int K = write_cheb(cb, lo, hi, dte, precision, cnt, count_step, c.work);
   if (tid == 0) {
-    cb[CHEB_BSCALE] = bscale;
+    cb[CHEB_BSCALE] = digits ? bscale : 0.0;
     if (K < 0) atomicOr(&L.fail, 2);
-    if (c.ips) {
-      c.ips[(size_t)t * kIpStride + IP_SUB] = 0.0f;
-      c.chebq[CHEBQ_LIST + atomicAdd(&c.chebq[CHEBQ_COUNT], 1)] = t;
-    }
+    if (c.ips) c.ips[(size_t)t * kIpStride + IP_SUB] = 0.0f;
+    if (c.ips || (c.i8_slabs && !c.path && !digits)) c.chebq[CHEBQ_LIST + atomicAdd(&c.chebq[CHEBQ_COUNT], 1)] = t;
   }
 }
 
@@ -803,9 +811,7 @@ __device__ void cheb_setup(const ClassDev& c, int t, const ModelAt& mm, double v
 // here), so e^{-M} takes a Taylor polynomial of two to four terms.
 //
 // The plan (s, terms p, P) comes from the neglected terms: with beta >= ||M||
-// (Montgomery and Vaughan's inequality for sum x_j x_k / (lambda_j -
-// lambda_k), constant 1.3154 pi (Preissmann), over the gaps delta_j to the
-// nearest neighbour), nu = t^2 (|a| + 2|b| ||V||) and the spread ||V|| of
+// (kHilbert, over the gaps delta_j to the nearest neighbour), nu = t^2 (|a| + 2|b| ||V||) and the spread ||V|| of
 // Lambda seen from the impurity, the third Magnus terms are below beta^2 nu t
 // ||V|| / 180 + beta nu^2 / 30 and the Gauss rule leaves 2 beta nu / 4 times
 // its weighted error; their sum may reach one FP32 rounding unit (2^-24; the
@@ -886,7 +892,7 @@ __device__ bool ip_setup(const ClassDev& c, int t, const ModelAt& mm, double vfa
   }
   // the plan (the same in every thread)
   const double vn = sqrt(red[2]);
-  const double bn = 1.3154 * 3.14159265358979324 * (fabs(a) * red[0] + 2.0 * fabs(b) * sqrt(red[0] * red[1]));
+  const double bn = kHilbert * (fabs(a) * red[0] + 2.0 * fabs(b) * sqrt(red[0] * red[1]));
   const double nn = fabs(a) + 2.0 * fabs(b) * vn;
   if (!((0.5 * (L.lam[n - 1] - L.lam[0]) + sqrt((double)n) * bn) * dte <= kIpMaxRho)) return false;
   int sub = 0, pairs = 1;

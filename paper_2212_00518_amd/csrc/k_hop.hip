@@ -1273,9 +1273,11 @@ __device__ void filter_one(const ClassDev& c, int t, double dt_run, uint64_t see
   const size_t base = (size_t)t * N * n_pad;
   double fro_part = 0.0;
   const int slabs_max = (N + 7) >> 3;
-  const float* ips = c.ips ? c.ips + (size_t)t * kIpStride : nullptr;
-  const int n_slabs = ips ? (ips[IP_SUB] != 0.0f ? slabs_max : (int)ips[IP_TERMS])
-                      : c.i8_slabs ? c.i8_slabs : c.n_slabs;
+  int n_slabs = c.n_slabs;
+  if (c.ips)
+    n_slabs = c.ips[(size_t)t * kIpStride + IP_SUB] != 0.0f ? slabs_max : c.chebq[CHEBQ_LIST + c.n_traj + t];
+  else if (c.i8_slabs)
+    n_slabs = c.cheb[(size_t)t * kChebStride + CHEB_BSCALE] != 0.0 ? c.i8_slabs : c.chebq[CHEBQ_LIST + c.n_traj + t];
   for (int b = tid; b < n_pad; b += kFltThreads) {
     double s2 = 0.0;
     if (c.rown) {

@@ -55,6 +55,8 @@ struct PropCfg<double> {
   static constexpr int kDepth = 2;
   static constexpr int kMaxColTiles = 3;
   static constexpr int kMaxPairs = 6;  // output tiles per wave (the slab width is capped to fit)
+  // waves per SIMD of the queue's tiers: as many as k_prop's registers allow
+  static constexpr int queue_waves(int q) { return q == 2 ? 6 : q == 3 ? 4 : q == 4 ? 3 : 2; }
   __device__ static inline acc_t mma(double a, double b, acc_t c) {
     return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
   }
@@ -70,6 +72,7 @@ struct PropCfg<float> {
   static constexpr int kDepth = 4;  // two-tile waves; wider ones use 2
   static constexpr int kMaxColTiles = 5;
   static constexpr int kMaxPairs = 9;  // output tiles per wave (the slab width is capped to fit)
+  static constexpr int queue_waves(int q) { return q == 2 ? 8 : q == 3 ? 7 : q == 6 ? 4 : 2; }
   __device__ static inline acc_t mma(float a, float b, acc_t c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
   }
@@ -283,12 +286,13 @@ __device__ void clenshaw_tiles(const Slab<T>& s, int t0, int tid) {
 // kLoop: called from a loop over items.  What does not depend on the item is
 // then hidden from the compiler, which would keep addresses and reciprocals of
 // it in registers across the loop (85 for 49, half the work-groups on a
-// compute unit).
+// compute unit).  And it is told what is the same in every lane: an item's
+// stores might alias the next one's numbers, which it then reads lane by lane.
 template <typename T, int kMode, int kQ, bool kLoop = false>
-__device__ void prop_item(const ClassDev& c, T* taps, int tap_k, int t, int slab, int n_slabs, unsigned char* smem_raw) {
+__device__ void prop_item(const ClassDev& c, const double* cheb, T* taps, int tap_k, int t, int slab, int n_slabs,
+                          unsigned char* smem_raw) {
   typedef PropCfg<T> Cfg;
-  if (t >= live_slots(c)) return;
-  if (c.status[t] & kFreezeMask) return;
+  if (__builtin_amdgcn_readfirstlane(t >= live_slots(c) || (c.status[t] & kFreezeMask))) return;
 
   const ModelDev& md = c.md;
   Slab<T> s;
@@ -311,8 +315,8 @@ __device__ void prop_item(const ClassDev& c, T* taps, int tap_k, int t, int slab
   s.Bt = Cfg::B(c) + (size_t)t * c.b_stride;
   T* Cg = Cfg::C(c) + (size_t)t * s.N * s.n_pad * 2;
   s.Cg = Cg;
-  s.cb = c.cheb + (size_t)t * kChebStride;
-  s.K = (int)s.cb[CHEB_K];
+  s.cb = cheb + (size_t)t * kChebStride;
+  s.K = __builtin_amdgcn_readfirstlane((int)s.cb[CHEB_K]);
   s.invr = (T)s.cb[CHEB_INVR];
   s.tap = taps ? taps + (size_t)t * tap_k * s.N * s.n_pad * 2 : nullptr;
   const T cc = (T)s.cb[CHEB_C];
@@ -406,12 +410,13 @@ __global__ __launch_bounds__(kPropThreads) void k_prop(ClassDev c, T* taps, int 
   extern __shared__ unsigned char smem_raw[];
   // XCD-aware id mapping: blocks b, b+8, b+16, ... share an XCD.
   const int local = blockIdx.x >> 3;
-  prop_item<T, kMode, kQ>(c, taps, tap_k, (local / c.n_slabs) * 8 + (blockIdx.x & 7), local % c.n_slabs, c.n_slabs,
+  prop_item<T, kMode, kQ>(c, c.cheb, taps, tap_k, (local / c.n_slabs) * 8 + (blockIdx.x & 7), local % c.n_slabs, c.n_slabs,
                           smem_raw);
 }
 
-// Classes on the interaction picture queue the trajectories that need the
-// series (c.chebq).  A launch of as many work-groups as are resident takes them:
+// The trajectories that need the series in a class on the interaction picture,
+// and those that need FP64 instructions in one on 8-bit digits, are queued
+// (c.chebq).  A launch of as many work-groups as are resident takes them:
 // slabs of one tile while the queue is short, else the class's own.  The
 // entries e, e + 8, ... belong to one XCD, whose work-groups (blocks b, b + 8,
 // ...) share a trajectory's B in its L2; each takes the XCD's next item when it
@@ -419,12 +424,13 @@ __global__ __launch_bounds__(kPropThreads) void k_prop(ClassDev c, T* taps, int 
 // queued: 12.6 ms a step, 12.4 with the series for all and no queue, 15.3 with
 // the items in fixed turns over all XCDs and 85 registers for 51.
 // The last work-group to finish resets the queue for the next propagator.
-template <int kQ>
+template <typename T, int kQ>
 __global__ __launch_bounds__(kPropThreads)
-    __attribute__((amdgpu_waves_per_eu(kQ == 2 ? 8 : kQ == 3 ? 7 : kQ == 6 ? 4 : 2))) void k_prop_queue(ClassDev c) {
+    __attribute__((amdgpu_waves_per_eu(PropCfg<T>::queue_waves(kQ)))) void k_prop_queue(ClassDev c, const double* __restrict__ cheb) {
   extern __shared__ unsigned char smem_raw[];
-  __shared__ int next;
-  const int count = c.chebq[CHEBQ_COUNT];
+  // in the items' LDS: a variable of its own would move theirs off alignment
+  int* next = reinterpret_cast<int*>(smem_raw);
+  const int count = __builtin_amdgcn_readfirstlane(c.chebq[CHEBQ_COUNT]);
   if (count == 0) return;  // nothing to reset either (14 us with the count of the work-groups done, 4 without)
   const int xcd = blockIdx.x & 7;
   const int tiles = (c.md.N + 7) >> 3;
@@ -433,12 +439,13 @@ __global__ __launch_bounds__(kPropThreads)
   for (int i = blockIdx.x >> 3; i < items;) {
     int ns = n_slabs;
     asm volatile("" : "+s"(ns));  // as in prop_item
-    const int t = c.chebq[CHEBQ_LIST + i / ns * 8 + xcd], slab = i % ns;
-    if (slab == 0 && threadIdx.x == 0) c.ips[(size_t)t * kIpStride + IP_TERMS] = (float)ns;
-    prop_item<float, kPropagate, kQ, true>(c, nullptr, 0, t, slab, ns, smem_raw);
-    if (threadIdx.x == 0) next = (int)(gridDim.x >> 3) + atomicAdd(&c.chebq[CHEBQ_NEXT + xcd], 1);
+    const int t = __builtin_amdgcn_readfirstlane(c.chebq[CHEBQ_LIST + i / ns * 8 + xcd]), slab = i % ns;
+    if (slab == 0 && threadIdx.x == 0) c.chebq[CHEBQ_LIST + c.n_traj + t] = ns;
+    prop_item<T, kPropagate, kQ, true>(c, cheb, nullptr, 0, t, slab, ns, smem_raw);
     __syncthreads();
-    i = __builtin_amdgcn_readfirstlane(next);
+    if (threadIdx.x == 0) *next = (int)(gridDim.x >> 3) + atomicAdd(&c.chebq[CHEBQ_NEXT + xcd], 1);
+    __syncthreads();
+    i = __builtin_amdgcn_readfirstlane(*next);
     __syncthreads();
   }
   if (threadIdx.x == 0 && atomicAdd(&c.chebq[CHEBQ_DONE], 1) == (int)gridDim.x - 1) {
@@ -471,10 +478,10 @@ template <typename T, int kMode>
 const void* prop_fn(int tier) {  // kMode -1: the queue kernel
   if constexpr (kMode < 0) {
     switch (tier) {
-      case 0: return (const void*)k_prop_queue<Tiers<T>::q[0]>;
-      case 1: return (const void*)k_prop_queue<Tiers<T>::q[1]>;
-      case 2: return (const void*)k_prop_queue<Tiers<T>::q[2]>;
-      default: return (const void*)k_prop_queue<Tiers<T>::q[3]>;
+      case 0: return (const void*)k_prop_queue<T, Tiers<T>::q[0]>;
+      case 1: return (const void*)k_prop_queue<T, Tiers<T>::q[1]>;
+      case 2: return (const void*)k_prop_queue<T, Tiers<T>::q[2]>;
+      default: return (const void*)k_prop_queue<T, Tiers<T>::q[3]>;
     }
   } else
 
@@ -537,11 +544,12 @@ hipError_t prop_prepare(const ClassDev& c, int precision) {
   const size_t lds = prop_lds_bytes(c, precision);
   if (lds <= 64 * 1024) return hipSuccess;
   for (int tier = 0; tier < 4; ++tier) {
-    const void* fns[3] = {nullptr, nullptr, nullptr};
+    const void* fns[4] = {};
     if (precision == IESH_FP64) {
       fns[0] = prop_fn<double, kPropagate>(tier);
       fns[1] = prop_fn<double, kClenshawTaps>(tier);
       fns[2] = prop_fn<double, kForwardTaps>(tier);
+      if (c.i8_slabs) fns[3] = prop_fn<double, -1>(tier);
     } else {
       fns[0] = c.ips ? prop_fn<float, -1>(tier) : prop_fn<float, kPropagate>(tier);
     }
@@ -600,19 +608,24 @@ hipError_t launch_prop_ip(const ClassDev& c, hipStream_t s) {
   return prop_ip::dispatch(c.md.n_pad / 16, prop_ip::Launch{&c, grid, c.ip_waves, c.ip_groups, s, false});
 }
 
-// The queued trajectories of an interaction-picture class.
-hipError_t launch_prop_queue(const ClassDev& c, hipStream_t s) {
+// The queued trajectories of a class.
+template <typename T>
+hipError_t launch_prop_queue_t(const ClassDev& c, dim3 grid, size_t lds, hipStream_t s) {
+  switch (prop_tier<T>(c)) {
+    case 0: hipLaunchKernelGGL((k_prop_queue<T, Tiers<T>::q[0]>), grid, dim3(kPropThreads), lds, s, c, c.cheb); break;
+    case 1: hipLaunchKernelGGL((k_prop_queue<T, Tiers<T>::q[1]>), grid, dim3(kPropThreads), lds, s, c, c.cheb); break;
+    case 2: hipLaunchKernelGGL((k_prop_queue<T, Tiers<T>::q[2]>), grid, dim3(kPropThreads), lds, s, c, c.cheb); break;
+    default: hipLaunchKernelGGL((k_prop_queue<T, Tiers<T>::q[3]>), grid, dim3(kPropThreads), lds, s, c, c.cheb); break;
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_prop_queue(const ClassDev& c, int precision, hipStream_t s) {
   if (c.n_live < 1) return hipSuccess;
   const int items = (c.n_live + 7) / 8 * 8 * ((c.md.N + 7) / 8);
   const dim3 grid(c.cheb_groups < items ? c.cheb_groups : items);
-  const size_t lds = prop_lds_bytes(c, IESH_MIXED);
-  switch (prop_tier<float>(c)) {
-    case 0: hipLaunchKernelGGL((k_prop_queue<Tiers<float>::q[0]>), grid, dim3(kPropThreads), lds, s, c); break;
-    case 1: hipLaunchKernelGGL((k_prop_queue<Tiers<float>::q[1]>), grid, dim3(kPropThreads), lds, s, c); break;
-    case 2: hipLaunchKernelGGL((k_prop_queue<Tiers<float>::q[2]>), grid, dim3(kPropThreads), lds, s, c); break;
-    default: hipLaunchKernelGGL((k_prop_queue<Tiers<float>::q[3]>), grid, dim3(kPropThreads), lds, s, c); break;
-  }
-  return hipGetLastError();
+  const size_t lds = prop_lds_bytes(c, precision);
+  return precision == IESH_FP64 ? launch_prop_queue_t<double>(c, grid, lds, s) : launch_prop_queue_t<float>(c, grid, lds, s);
 }
 
 // FP64 tap modes for the adjoint: mode 1 stores the Clenshaw vectors b_K .. b_1

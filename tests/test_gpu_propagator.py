@@ -201,14 +201,16 @@ def test_steps_beyond_the_series_stay_refused(M, N, dt, accepted):
 # more items than work-groups, in slabs of three tiles and of one, of the first
 # and the second register tier, and fewer; the queue is filled anew by every
 # sub-step
+@pytest.mark.parametrize("precision,tol", [("mixed", 4e-6), ("fp64", 1e-12)])
 @pytest.mark.parametrize("substeps", [1, 2])
 @pytest.mark.parametrize("name,M,N,T", [("c3", 40, 20, 1500), ("c2", 100, 50, 300), ("c3", 160, 80, 160),
                                         ("c2", 260, 40, 320), ("c2", 100, 50, 24)])
-def test_long_queues_of_the_series(name, M, N, T, substeps):
-    """Ensembles of which two thirds are too fast for the interaction picture,
-    over three steps: a sample against the oracle (the Chebyshev series' 4e-6
-    for each of its up to six propagations), and all states bit by bit with and
-    without the no-hop bound, which reads the row norms by slab."""
+def test_long_queues_of_the_series(name, M, N, T, substeps, precision, tol):
+    """Ensembles of which two thirds are too fast for the interaction picture
+    and for 8-bit digits, over three steps: a sample against the oracle (the
+    series' bound for each of its up to six propagations), and all states bit
+    by bit with and without the no-hop bound, which reads the row norms by
+    slab."""
     cfg = make_cfg(name, M=M, N=N)
     m = models.from_config(cfg, M=M)
     steps = 3
@@ -219,7 +221,7 @@ def test_long_queues_of_the_series(name, M, N, T, substeps):
     states = [dyn.State([x[t]], [v[t]], C[t % 8], np.arange(N)) for t in range(T)]
     out = []
     for off in (0, 1):
-        ens = ensemble(cfg, T, precision="mixed", elec_substeps=substeps, lowdin_every=0, hop_filter_off=off)
+        ens = ensemble(cfg, T, precision=precision, elec_substeps=substeps, lowdin_every=0, hop_filter_off=off)
         upload(ens, states)
         ens.run(steps)
         out.append(ens.get_state())
@@ -236,6 +238,41 @@ def test_long_queues_of_the_series(name, M, N, T, substeps):
         if not np.array_equal(out[0][3][t][:N], ref.s):
             continue  # another hop
         err = np.max(np.abs(unpack_C(out[0][2], t, m.n, N, m.n, N) - ref.C))
-        assert err <= 4e-6 * steps * substeps, (t, err)
+        assert err <= tol * steps * substeps, (t, err)
         ok += 1
     assert ok >= 6
+
+
+@pytest.mark.parametrize("name,M,N,v,dt_factor", [("c2", 120, 60, 0.07, 8.0), ("c2", 200, 100, 0.07, 8.0),
+                                                  ("c3", 160, 80, 0.3, 1.0), ("c3", 320, 160, 0.3, 1.0)])
+def test_fast_fp64_steps_keep_orbitals_orthogonal(name, M, N, v, dt_factor):
+    """One FP64 step of unit orbitals.  An FP64 series of K <= 62 terms rounds
+    every element by at most K units of 2^-53 of itself, so the overlaps of
+    different orbitals, 2 Re <C_j, dC_k> with C_j near a unit vector, stay
+    within 2 K 2^-53 of the orbitals' other elements (rms over all pairs).
+    Fixed-point products, whose error is relative to the largest element,
+    exceed that on a fast step."""
+    cfg = make_cfg(name, M=M, N=N)
+    cfg["dt"] *= dt_factor
+    m = models.from_config(cfg, M=M)
+    T = 4
+    xs = np.linspace(4.0, 4.3, T) if name == "c3" else np.linspace(0.0, 2.0, T)
+    states = [dyn.State([xs[t]], [v], np.eye(m.n, N, dtype=np.complex128), np.arange(N)) for t in range(T)]
+    ens = ensemble(cfg, T)
+    upload(ens, states)
+    ens.step()
+    Cf = ens.get_state()[2]
+    assert np.all(ens.status() == 0)
+    ens.close()
+    from paper_2212_00518_amd import unpack_C
+    off = ~np.eye(N, dtype=bool)
+    overlap, rest = [], []
+    for t in range(T):
+        C = unpack_C(Cf, t, m.n, N, m.n, N)
+        re, im = C.real.astype(np.longdouble), C.imag.astype(np.longdouble)
+        G = np.hypot(re.T @ re + im.T @ im, re.T @ im - im.T @ re)
+        overlap.append(np.sqrt(np.mean(G[off] ** 2)))
+        rest.append(np.sqrt(np.mean(np.abs(C - np.eye(m.n, N) * C) ** 2)))
+    a, b = float(np.mean(overlap)), float(np.mean(rest))
+    print(f"{name} M={M}: overlaps {a:.2e}, bound {2 * 62 * 2.0 ** -53 * b:.2e}", flush=True)
+    assert a <= 2 * 62 * 2.0 ** -53 * b
