@@ -245,7 +245,8 @@ __device__ inline void sub_intervals(const Group& gr, float (&x)[RT][4]) {
     m = fmaxf(m, __shfl_xor(m, 16));
     m = fmaxf(m, __shfl_xor(m, 32));
     int ex = 0;
-    if (m > 0x1p-100f && m < 0x1p100f) (void)frexpf(m, &ex);
+    if (m > 0.0f && m <= 3.4028234e38f) (void)frexpf(m, &ex);
+    ex = max(ex, -115);  // FP32 holds the scale and its inverse
     const float sx = ldexpf(1.0f, 10 - ex);
     apply_small<R>(P, T, ips, -sg);
 #pragma unroll

@@ -276,3 +276,36 @@ def test_fast_fp64_steps_keep_orbitals_orthogonal(name, M, N, v, dt_factor):
     a, b = float(np.mean(overlap)), float(np.mean(rest))
     print(f"{name} M={M}: overlaps {a:.2e}, bound {2 * 62 * 2.0 ** -53 * b:.2e}", flush=True)
     assert a <= 2 * 62 * 2.0 ** -53 * b
+
+
+@pytest.mark.parametrize("M,N", [(15, 8), (54, 23), (200, 100)])
+@pytest.mark.parametrize("scale", [0.0, 2.0 ** -60, 2.0 ** 120, 2.0 ** -104])
+def test_mixed_orbitals_keep_their_scale(M, N, scale):
+    """The same of the mixed path, planned and queued trajectories, over the
+    range of FP32: bit by bit, and at 2^-104, where the smallest elements leave
+    the range, within 2^-45 of an orbital's norm and the tolerance of a step."""
+    cfg = make_cfg("c2", M=M, N=N)
+    m = models.from_config(cfg, M=M)
+    states = random_states(m, N, 3, seed=5 + M, xs=[-2.0, 3.0, 1.0], v_scale=2e-3)
+    states[2].v[0] = 0.05
+    from paper_2212_00518_amd import unpack_C
+    out = []
+    for f in (1.0, scale):
+        ens = ensemble(cfg, 3, precision="mixed", lowdin_every=0)
+        for s in states:
+            s.C = s.C.astype(np.complex64).astype(np.complex128)
+            s.C[:, ::3] *= f
+        upload(ens, states)
+        ens.step()
+        C = ens.get_state()[2]
+        out.append([unpack_C(C, t, m.n, N, ens.n_max, ens.N_max) for t in range(3)])
+        ens.close()
+    for t in range(3):
+        if scale == 2.0 ** -104:
+            got = out[1][t].copy()
+            got[:, ::3] /= scale
+            assert np.max(np.abs(got - out[0][t])) <= (1e-6 if t < 2 else 4e-6)
+        else:
+            want = out[0][t].copy()
+            want[:, ::3] *= scale
+            assert np.array_equal(out[1][t], want)
