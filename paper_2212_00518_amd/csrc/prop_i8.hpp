@@ -232,7 +232,8 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     nrm[ct] += __shfl_xor(nrm[ct], 32);
     nrm[ct] += swap8(nrm[ct]);  // both parts
   }
-  // scale of each orbital: a power of two above its norm
+  // scale of each orbital: a power of two above its norm, or by its largest
+  // element where the squares leave the range
   double* part = reinterpret_cast<double*>(smem);  // [waves][NCT][16]
   if (g == 0)
 #pragma unroll
@@ -240,6 +241,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   __syncthreads();
   if (bscale == 0.0) return;  // left to the FP64 instructions
   double sx[NCT], isx[NCT];
+  int odd = 0;  // of this lane's columns
 #pragma unroll
   for (int ct = 0; ct < NCT; ++ct) {
     double s = 0.0;
@@ -248,7 +250,39 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     (void)frexp(sqrt(s), &ex);
     sx[ct] = s > 0.0 ? ldexp(1.0, ex) : 1.0;
     isx[ct] = 1.0 / sx[ct];
-    if (!(s <= 0x1.fffffffffffffp1023)) sx[ct] = s - s;  // not a number, as the result then is
+    if (!(s >= 0x1p-900 && s <= 0x1p900) && (slab * NCT + ct) * 8 + (lane & 7) < N) odd |= 1 << ct;
+  }
+  if (__any(odd != 0)) {  // the same in every wave
+    __syncthreads();
+    double* part = reinterpret_cast<double*>(smem);
+#pragma unroll
+    for (int ct = 0; ct < NCT; ++ct) {
+      double m = 0.0;
+#pragma unroll
+      for (int i = 0; i < NR; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) m = fabs(X[i][ct][r]) > m || X[i][ct][r] != X[i][ct][r] ? fabs(X[i][ct][r]) : m;
+      for (int sh = 8; sh < 64; sh <<= 1) {
+        const double o = __shfl_xor(m, sh);
+        m = o > m || o != o ? o : m;
+      }
+      if (g == 0) part[(wave * NCT + ct) * 16 + col] = m;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int ct = 0; ct < NCT; ++ct) {
+      double m = 0.0;
+      for (int w = 0; w < W; ++w) {
+        const double o = part[(w * NCT + ct) * 16 + col];
+        m = o > m || o != o ? o : m;
+      }
+      if (!(odd >> ct & 1)) continue;
+      int ex = 0;
+      (void)frexp(m, &ex);  // 2 n elements: the norm is below 2^5 of the largest
+      sx[ct] = m > 0.0 ? ldexp(1.0, min(max(ex + 5, -1000), 1020)) : 1.0;
+      isx[ct] = 1.0 / sx[ct];
+      if (!(m <= 0x1.fffffffffffffp1023)) sx[ct] = m - m;  // not a number, as the result then is
+    }
   }
   __syncthreads();
   for (int i = tid; i < buf_bytes / 8; i += 64 * W) reinterpret_cast<i4*>(smem)[i] = i4{0, 0, 0, 0};

@@ -309,3 +309,29 @@ def test_mixed_orbitals_keep_their_scale(M, N, scale):
             want = out[0][t].copy()
             want[:, ::3] *= scale
             assert np.array_equal(out[1][t], want)
+
+
+# every shape of work-group, with an orbital tile that is partly empty
+@pytest.mark.parametrize("M,N", [(111, 41), (130, 20), (200, 100), (320, 60)])
+@pytest.mark.parametrize("scale", [2.0 ** 600, 2.0 ** -600])
+def test_fp64_orbitals_whose_squares_leave_the_range(M, N, scale):
+    """Scaled orbitals and the others beside them, within 1e-12 of their norm
+    of the unscaled ones' result."""
+    cfg = make_cfg("c2", M=M, N=N)
+    m = models.from_config(cfg, M=M)
+    states = random_states(m, N, 2, seed=5 + M, xs=[-2.0, 3.0], v_scale=2e-3)
+    from paper_2212_00518_amd import unpack_C
+    out = []
+    for f in (1.0, scale):
+        ens = ensemble(cfg, 2)
+        for s in states:
+            s.C[:, ::3] *= f
+        upload(ens, states)
+        ens.step()
+        C = ens.get_state()[2]
+        out.append([unpack_C(C, t, m.n, N, ens.n_max, ens.N_max) for t in range(2)])
+        ens.close()
+    for t in range(2):
+        got = out[1][t].copy()
+        got[:, ::3] /= scale
+        assert np.max(np.abs(got - out[0][t])) <= 1e-12
