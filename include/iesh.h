@@ -371,9 +371,10 @@ int iesh_set_step_caps(iesh_ctx* ctx, const int64_t* caps);
 /* Per bath-size class (model index cls), 8 int32 values: number of
    trajectories, live slots (the step kernels visit slots [0, live); the
    others hold frozen trajectories after compaction), n, N, orbital tiles of
-   16 columns per propagation work-group (chosen by timing at creation),
-   propagation work-groups per trajectory, n rounded up to 16, 0.  Does not
-   synchronise. */
+   16 columns per propagation work-group, propagation work-groups per
+   trajectory (those of the kernel the class's trajectories take unless they
+   are too fast for it; the dense kind's and FP64 below 7 row tiles are chosen
+   by timing at creation), n rounded up to 16, 0.  Does not synchronise. */
 int iesh_class_info(const iesh_ctx* ctx, int32_t cls, int32_t* info);
 
 typedef struct iesh_sizes {

@@ -1123,8 +1123,8 @@ int iesh_class_info(const iesh_ctx* ctx, int32_t cls, int32_t* info) {
   info[1] = ctx->live_host[cls];
   info[2] = c.md.n;
   info[3] = c.md.N;
-  info[4] = c.nct_max;
-  info[5] = c.n_slabs;
+  info[4] = c.ips ? c.ip_waves : c.i8_slabs ? prop_i8_tiles(c) : c.nct_max;
+  info[5] = c.ips ? c.ip_groups : c.i8_slabs ? c.i8_slabs : c.n_slabs;
   info[6] = c.md.n_pad;
   info[7] = 0;
   return IESH_OK;

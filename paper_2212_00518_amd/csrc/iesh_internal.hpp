@@ -389,6 +389,7 @@ hipError_t prop_prepare(const ClassDev& c, int precision);
 // FP64 propagation in 8-bit digits: sets i8_slabs where the class takes it; its B per trajectory
 size_t i8_b_doubles(int n_pad);
 hipError_t i8_prepare(ClassDev& c);
+int prop_i8_tiles(const ClassDev& c);  // orbital tiles of a work-group
 hipError_t launch_prop_i8(const ClassDev& c, hipStream_t s);
 size_t prop_lds_bytes(const ClassDev& c, int precision);
 hipError_t launch_hop(const ClassDev& c, double dt, uint64_t seed, Counters* cnt,

@@ -574,6 +574,8 @@ hipError_t launch_prop(const ClassDev& c, int precision, hipStream_t s) {
 // FP64 in 8-bit digits.
 size_t i8_b_doubles(int n_pad) { return prop_i8::chosen(n_pad) ? prop_i8::b_doubles(n_pad) : 0; }
 
+int prop_i8_tiles(const ClassDev& c) { return prop_i8::shape(c.md.n_pad).nct; }
+
 hipError_t i8_prepare(ClassDev& c) {
   if (!prop_i8::chosen(c.md.n_pad)) return hipSuccess;
   const int nct = prop_i8::shape(c.md.n_pad).nct;

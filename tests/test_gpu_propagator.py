@@ -335,3 +335,16 @@ def test_fp64_orbitals_whose_squares_leave_the_range(M, N, scale):
         got = out[1][t].copy()
         got[:, ::3] /= scale
         assert np.max(np.abs(got - out[0][t])) <= 1e-12
+
+
+@pytest.mark.parametrize("precision,M,N,tiles,groups", [
+    ("mixed", 200, 100, 7, 2), ("mixed", 320, 160, 4, 5), ("mixed", 40, 20, 3, 1),
+    ("fp64", 200, 100, 2, 7), ("fp64", 130, 20, 1, 3), ("fp64", 320, 160, 1, 20)])
+def test_class_info_names_the_running_shape(precision, M, N, tiles, groups):
+    """Work-groups of one trajectory's ceil(N / 8) orbital tiles: the
+    interaction picture's waves with a tile each (at most 8, beyond 13 row
+    tiles 4), the digit kernel's one or two tiles."""
+    ens = ensemble(make_cfg("c2", M=M, N=N), 4, precision=precision)
+    info = ens.class_info(0)
+    ens.close()
+    assert (info["tiles_per_group"], info["groups_per_traj"]) == (tiles, groups), info
