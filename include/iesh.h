@@ -486,7 +486,7 @@ int iesh_sync(iesh_ctx* ctx);
    that is not an arrowhead (Eq. single_electron_discrete_electronic_hamiltonian
    for H of any structure).  Cyclic two-sided Jacobi rotations, FP64, one
    work-group per matrix with everything in LDS up to IESH_JACOBI_LDS_N; beyond,
-   two kernels per sweep with a device workspace (2 m (m + 1) doubles per
+   two kernels for each of the first 16 sweeps and one for the others, with a device workspace (2 m (m + 1) doubles per
    matrix, m = n rounded up to even; the call allocates it, waits for the
    kernels and frees it) and Q as scratch until the vectors are written.
      H      : batch x n x n row-major (only symmetric input is meaningful)

@@ -29,12 +29,16 @@
 // fits; the diagonal lives in registers), and writes the sweep's rotations to
 // memory; k_jacobi_vectors then applies them to V, whose rows are independent:
 // a wave takes kRows of them through the whole sweep in LDS, without barriers.
-// The host launches both for every sweep; those of a converged matrix return
-// at once.  Past n = 201 a sweep works on all of A
+// The host launches both for each of the first kPairs sweeps, where those of a
+// converged matrix return at once, and one more kernel that makes what is left
+// in a work-group a matrix (2 us for each launch that has nothing to do: with
+// 60 pairs a diagonal matrix of n = 97 took 0.43 ms, now 0.19).  Past n = 201 a sweep works on all of A
 // in memory (its triangle alone took 2.3 times as long), still
 // without V.  Measured with the copies of a call, one kernel for all / now:
 // 128 matrices of n = 97 7.5 / 4.3 ms, of 201 53.5 / 20.5, of 320 196 / 134, one
 // of 201 44 / 10.
+
+#include <algorithm>
 
 #include "iesh_internal.hpp"
 
@@ -50,6 +54,9 @@ constexpr int kJacWaves = kJacThreads / 64;
 constexpr double kSmallRot = 1e-8;
 
 constexpr int kMaxSweeps = 60;
+// Sweeps with a pair of kernels of their own: random matrices of n = 97 to 336
+// take 9 to 11, singular ones 10 to 18 (23 at most of those tried).
+constexpr int kPairs = 16;
 
 // LDS bytes of k_jacobi: A and V, the rotations of a round and the pairs.
 size_t jacobi_lds(int n) {
@@ -210,12 +217,13 @@ constexpr int kSlots = (kMaxStates / 2 + 63) / 64;  // pairs of a round to a lan
 constexpr size_t kJacLds = 160 * 1024;
 
 // A matrix in the work space (2 m (m + 1) doubles): V, A, its diagonal, and
-// the number of the sweep that converged (0: none yet).  A is the strict
+// the number of the sweep that converged (0: none yet) and whether the last one
+// rotated.  A is the strict
 // lower triangle (row i at i (i - 1) / 2) and one element that stays zero, or,
 // past the order whose triangle fits into the LDS, the whole [m][m].
 struct JacWork {
   double *V, *A, *diag;
-  int32_t* done;
+  int32_t *done, *rotated;
 };
 
 __host__ __device__ constexpr int tri_size(int n) { return n * (n - 1) / 2; }
@@ -227,6 +235,7 @@ __device__ inline JacWork jac_work(double* work, int n, int b) {
   JacWork w;
   w.diag = work + (size_t)b * 2 * m * (m + 1);
   w.done = reinterpret_cast<int32_t*>(w.diag + n);
+  w.rotated = w.done + 1;
   w.V = w.diag + n + 1;
   w.A = w.V + (size_t)n * n;
   return w;
@@ -254,14 +263,11 @@ __device__ inline void jac_pair(int r, int k, int m, int& p, int& q) {
 // Bound by the vector instructions of the blocks (about 80 each, a quarter of
 // them FP64), then by the rotations' serial chain.  The triangle's row offsets
 // are triangular numbers, which spread a column walk over all LDS banks.
-__global__ __launch_bounds__(kJacThreads) void k_jacobi_sweep(const double* __restrict__ H, int n, double* Q,
-                                                             double* work, int sweep) {
-  extern __shared__ double sm[];
-  const int b = blockIdx.x, tid = threadIdx.x;
+__device__ __forceinline__ void sweep_lds(const double* __restrict__ H, int n, double* Q, const JacWork& w, int b, int sweep,
+                                          double* sm) {
+  const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int m = n + (n & 1), half = m / 2, odd = n & 1, nt = tri_size(n);
-  const JacWork w = jac_work(work, n, b);
-  if (sweep > 0 && *w.done != 0) return;
   double* T = sm;            // strict lower triangle, [nt] is zero
   double* cs = sm + nt + 1;  // [half] cosine, sine
   int* pq = reinterpret_cast<int*>(cs + 2 * half);  // [half] p + (q << 16)
@@ -402,22 +408,30 @@ __global__ __launch_bounds__(kJacThreads) void k_jacobi_sweep(const double* __re
         if (y < n) w.diag[y] = dy[u];
       }
     }
-    const bool more = __any(any) && __any(large);
-    if (lane == 0) *w.done = more ? 0 : sweep + 1;
+    const bool some = __any(any), more = some && __any(large);
+    if (lane == 0) {
+      *w.done = more ? 0 : sweep + 1;
+      *w.rotated = some;
+    }
   }
+}
+
+__global__ __launch_bounds__(kJacThreads) void k_jacobi_sweep(const double* __restrict__ H, int n, double* Q,
+                                                             double* work, int sweep) {
+  extern __shared__ double sm[];
+  const JacWork w = jac_work(work, n, blockIdx.x);
+  if (sweep > 0 && *w.done != 0) return;
+  sweep_lds(H, n, Q, w, blockIdx.x, sweep, sm);
 }
 
 // The same with all of A in memory, where a round reads and writes it once:
 // rows of a pair by lanes along the columns, both triangles.
-__global__ __launch_bounds__(kJacThreads) void k_jacobi_sweep_mem(const double* __restrict__ H, int n, double* Q,
-                                                                 double* work, int sweep) {
+__device__ __forceinline__ void sweep_mem(const double* __restrict__ H, int n, double* Q, const JacWork& w, int b, int sweep) {
   __shared__ double cs[kMaxStates / 2], sn[kMaxStates / 2];
   __shared__ int pq[kMaxStates], flag[2];  // a rotation, a rotation above kSmallRot
-  const int b = blockIdx.x, tid = threadIdx.x;
+  const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int m = n + (n & 1), half = m / 2, odd = n & 1, np = n / 2;
-  const JacWork w = jac_work(work, n, b);
-  if (sweep > 0 && *w.done != 0) return;
   double* A = w.A;
   double* rot = jac_rot(Q, n, b);
   if (sweep == 0) {
@@ -476,20 +490,27 @@ __global__ __launch_bounds__(kJacThreads) void k_jacobi_sweep_mem(const double* 
     __syncthreads();
   }
   if (tid < n) w.diag[tid] = A[tid * m + tid];
-  if (tid == 0) *w.done = flag[0] && flag[1] ? 0 : sweep + 1;
+  if (tid == 0) {
+    *w.done = flag[0] && flag[1] ? 0 : sweep + 1;
+    *w.rotated = flag[0];
+  }
 }
 
-// V <- V J over the rotations of one sweep, kRows rows to a wave.  Bound by
-// the LDS (each round reads and writes every element of V once).
-__global__ __launch_bounds__(64) void k_jacobi_vectors(int n, int groups, double* Q, double* work, int sweep) {
-  extern __shared__ double row[];  // [kRows][n]
-  const int b = blockIdx.x / groups, lane = threadIdx.x, ld = n;
+__global__ __launch_bounds__(kJacThreads) void k_jacobi_sweep_mem(const double* __restrict__ H, int n, double* Q,
+                                                                 double* work, int sweep) {
+  const JacWork w = jac_work(work, n, blockIdx.x);
+  if (sweep > 0 && *w.done != 0) return;
+  sweep_mem(H, n, Q, w, blockIdx.x, sweep);
+}
+
+// V <- V J over the rotations of one sweep, kRows rows from i0 on, by one wave
+// with row: LDS [kRows][n].  Bound by the LDS (each round reads and writes every
+// element of V once).
+__device__ __forceinline__ void rotate_rows(int n, const double* rot, const JacWork& w, int i0, int sweep, double* row) {
+  const int lane = threadIdx.x & 63, ld = n;
   const int m = n + (n & 1), half = m / 2, odd = n & 1, np = n / 2;
-  const JacWork w = jac_work(work, n, b);
-  const int done = *w.done;
-  if (done != 0 && done != sweep + 1) return;  // converged before this sweep
-  const int i0 = (blockIdx.x - b * groups) * kRows;
-  const double* rot = jac_rot(Q, n, b);
+  const bool rotated = *w.rotated != 0;
+  if (!rotated && sweep > 0) return;
   for (int x = 0; x < kRows; ++x)
     for (int j = lane; j < n; j += 64)
       row[x * ld + j] = sweep == 0 || i0 + x >= n ? (j == i0 + x ? 1.0 : 0.0) : w.V[(size_t)(i0 + x) * n + j];
@@ -507,8 +528,8 @@ __global__ __launch_bounds__(64) void k_jacobi_vectors(int n, int groups, double
       }
     }
   };
-  load(0);
-  for (int r = 0; r < m - 1; ++r) {
+  if (rotated) load(0);
+  for (int r = 0; r < m - 1 && rotated; ++r) {
     double cc[kSlots], ss[kSlots];
 #pragma unroll
     for (int u = 0; u < kSlots; ++u) {
@@ -541,6 +562,39 @@ __global__ __launch_bounds__(64) void k_jacobi_vectors(int n, int groups, double
   __builtin_amdgcn_wave_barrier();
   for (int x = 0; x < kRows && i0 + x < n; ++x)
     for (int j = lane; j < n; j += 64) w.V[(size_t)(i0 + x) * n + j] = row[x * ld + j];
+}
+
+__global__ __launch_bounds__(64) void k_jacobi_vectors(int n, int groups, double* Q, double* work, int sweep) {
+  extern __shared__ double row[];
+  const int b = blockIdx.x / groups;
+  const JacWork w = jac_work(work, n, b);
+  const int done = *w.done;
+  if (done != 0 && done != sweep + 1) return;  // converged before this sweep
+  rotate_rows(n, jac_rot(Q, n, b), w, (blockIdx.x - b * groups) * kRows, sweep, row);
+}
+
+// The sweeps from `first` on of the matrices that need them, A and V in one
+// work-group (`waves` of it share the rows of V, as many as their LDS holds).
+template <bool kTri>
+__global__ __launch_bounds__(kJacThreads) void k_jacobi_rest(const double* __restrict__ H, int n, double* Q, double* work,
+                                                            int first, int waves) {
+  extern __shared__ double sm[];
+  const int b = blockIdx.x, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const JacWork w = jac_work(work, n, b);
+  if (*w.done != 0) return;
+  for (int sweep = first; sweep < kMaxSweeps; ++sweep) {
+    if constexpr (kTri)
+      sweep_lds(H, n, Q, w, b, sweep, sm);
+    else
+      sweep_mem(H, n, Q, w, b, sweep);
+    __syncthreads();  // A's and V's parts of the LDS are the same, and V reads the sweep's rotations
+    if (wave < waves)
+      for (int i0 = wave * kRows; i0 < n; i0 += waves * kRows)
+        rotate_rows(n, jac_rot(Q, n, b), w, i0, sweep, sm + (size_t)wave * kRows * n);
+    const int done = *w.done;
+    __syncthreads();  // every wave has read it, and left V's part, before the next sweep
+    if (done != 0) break;
+  }
 }
 
 // Ascending order (ties by index) and the phase: the first component of each
@@ -593,17 +647,26 @@ hipError_t launch_jacobi_large(const double* H, int n, int batch, double* lam, d
   const size_t lds = jacobi_sweep_lds(n), vlds = sizeof(double) * kRows * n;
   const bool tri = lds <= kJacLds;
   const int groups = (n + kRows - 1) / kRows;
-  hipError_t e = hipSuccess;
-  if (tri)
+  // LDS of the kernel for the rest (beside sweep_mem's own arrays)
+  const size_t own = tri ? 0 : sizeof(double) * kMaxStates + sizeof(int) * (kMaxStates + 2) + 64;
+  const int waves = (int)std::min<size_t>(kJacWaves, (kJacLds - own) / vlds);
+  const size_t rlds = std::max(tri ? lds : 0, waves * vlds);
+  const void* rest = tri ? (const void*)k_jacobi_rest<true> : (const void*)k_jacobi_rest<false>;
+  hipError_t e = hipFuncSetAttribute(rest, hipFuncAttributeMaxDynamicSharedMemorySize, (int)rlds);
+  if (e == hipSuccess && tri)
     e = hipFuncSetAttribute((const void*)k_jacobi_sweep, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  for (int sweep = 0; sweep < kMaxSweeps; ++sweep) {
+  for (int sweep = 0; sweep < kPairs; ++sweep) {
     if (tri)
       hipLaunchKernelGGL(k_jacobi_sweep, dim3(batch), dim3(kJacThreads), lds, s, H, n, Q, work, sweep);
     else
       hipLaunchKernelGGL(k_jacobi_sweep_mem, dim3(batch), dim3(kJacThreads), 0, s, H, n, Q, work, sweep);
     hipLaunchKernelGGL(k_jacobi_vectors, dim3(batch * groups), dim3(64), vlds, s, n, groups, Q, work, sweep);
   }
+  if (tri)
+    hipLaunchKernelGGL(k_jacobi_rest<true>, dim3(batch), dim3(kJacThreads), rlds, s, H, n, Q, work, kPairs, waves);
+  else
+    hipLaunchKernelGGL(k_jacobi_rest<false>, dim3(batch), dim3(kJacThreads), rlds, s, H, n, Q, work, kPairs, waves);
   hipLaunchKernelGGL(k_jacobi_order, dim3(batch), dim3(kJacThreads), 0, s, n, lam, Q, sweeps, work);
   return hipGetLastError();
 }
