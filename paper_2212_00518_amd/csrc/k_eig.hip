@@ -814,8 +814,13 @@ __device__ void cheb_setup(const ClassDev& c, int t, const ModelAt& mm, double v
 // (kHilbert, over the gaps delta_j to the nearest neighbour), nu = t^2 (|a| + 2|b| ||V||) and the spread ||V|| of
 // Lambda seen from the impurity, the third Magnus terms are below beta^2 nu t
 // ||V|| / 180 + beta nu^2 / 30 and the Gauss rule leaves 2 beta nu / 4 times
-// its weighted error; their sum may reach one FP32 rounding unit (2^-24; the
-// measured truncation is a fifth of the sum or less), the Taylor tail 2^-27.
+// its weighted error; their sum may reach one FP32 rounding unit (2^-24), the
+// Taylor tail 2^-27.  Against the exact exponential, over 2000 trajectories at
+// dt = 5 (scattering), 20 and 50: at most 2.5e-8 (2^-25.2), rms 3e-9; at up to ten
+// times those steps 4.5e-8 and 6e-9.  With both in one trajectory's orbitals,
+// rounding and truncation, the error of 1 to 400 steps is 0.1 to 0.75 times that
+// of the FP32 series, whose tail stays below 2^-26; a bound of 2^-26 here leaves
+// it as it is and takes 15% more of a scattering step.
 // A trajectory that needs more than three sub-intervals takes the Chebyshev
 // series, and so does one for which the series might need more than its most
 // terms: whether such a step is refused is the series' to say.
@@ -831,7 +836,7 @@ constexpr double kIpMaxRho = 35.0;
 // 1 - u^2 on [-1, 1]: sqrt(1/5); sqrt((7 -+ 2 sqrt 7) / 21), weights
 // (14 +- sqrt 7)/30 (1 - u^2)
 constexpr double kIpNode[2][2] = {{0.44721359549995794, 0.0}, {0.28523151648064510, 0.76505532392946469}};
-constexpr double kIpWeight[2][2] = {{2.0 / 3.0, 0.0}, {0.50971675, 0.15694991}};
+constexpr double kIpWeight[2][2] = {{2.0 / 3.0, 0.0}, {0.5097167540709727, 0.15694991259569394}};
 
 __device__ bool ip_setup(const ClassDev& c, int t, const ModelAt& mm, double vfac, double dte,
                          EigLds& L, Counters* cnt, bool count_step) {
