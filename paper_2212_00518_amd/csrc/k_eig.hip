@@ -58,7 +58,7 @@ struct EigLds {
 // 1/d from the hardware reciprocal estimate and two Newton steps
 // r <- r + r (1 - d r) (each squares the relative error).  Measured on gfx950
 // over 4M values spanning 1e-9 .. 5e8: the estimate is within 4.7e-8, one
-// step within 2.2e-15, two steps within 1.2e-16 (one unit in the last place).
+// step (rcp_nr1) within 2.2e-15, two steps within 1.2e-16 (one unit in the last place).
 // d != 0 at every call (poles are excluded from the root brackets, the
 // secular poles are distinct and the roots interlace them strictly).
 __device__ inline double rcp_nr(double d) {
@@ -67,12 +67,6 @@ __device__ inline double rcp_nr(double d) {
   r = fma(r, e, r);
   e = fma(-d, r, 1.0);
   return fma(r, e, r);
-}
-
-// The same with one Newton step (within 2.2e-15): the secular sums.
-__device__ inline double rcp_nr1(double d) {
-  const double r = __builtin_amdgcn_rcp(d);
-  return fma(r, fma(-d, r, 1.0), r);
 }
 
 // Sum of a value over the work-group, the same in every thread: one barrier and

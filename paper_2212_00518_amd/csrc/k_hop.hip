@@ -1228,13 +1228,6 @@ struct FltLds {
   int n_uocc;
 };
 
-// 1/d from the hardware estimate (within 4.7e-8) and one Newton step (within
-// 2.2e-15; the bound's own slack is 1e-10).
-__device__ inline double rcp_step(double d) {
-  const double r = __builtin_amdgcn_rcp(d);
-  return fma(r, fma(-d, r, 1.0), r);
-}
-
 template <bool kF32, bool kDense>
 __device__ void filter_one(const ClassDev& c, int t, double dt_run, uint64_t seed, Counters* cnt,
                            int record, int exit_enabled, double exit_x, int64_t max_steps,
@@ -1332,7 +1325,7 @@ __device__ void filter_one(const ClassDev& c, int t, double dt_run, uint64_t see
         const double gab = kDense ? (fabs(L.lam[a] - lb) <= gtol ? 0.0 : Gd[(size_t)b * n_pad + a])
                                   : qb * L.q0[a] * (dh + rho * (mub + (L.lam[a] - h)));
         if (gab != 0.0) {
-          const double d = v * gab * rcp_step(L.lam[a] - lb);
+          const double d = v * gab * rcp_nr1(L.lam[a] - lb);
           s = fma(d, d, s);
         }
       }
