@@ -12,12 +12,13 @@ determinant-ratio evaluation, so early steps are cheaper than the steady
 state.  The 100 timed steps span one period of the Loewdin correction of
 the mixed path.
 
-Both precisions are timed: the mixed path (FP32 MFMA propagation, FP64
-eigen-solve / overlap inverse / rescaling, FP64 Loewdin every 100 steps)
-gives the headline value; the FP64 path is reported beside it with the
-deviation of the mixed path from it.  The JSON line also carries the
-roofline of the dominant kernel (the orbital propagation) and the CPU
-oracle timed on the host cores on a bounded sample of the same workload.
+Both precisions are timed: the mixed path (FP32 orbitals, their products in
+pairs of f16 on the matrix cores, FP64 eigen-solve / overlap inverse /
+rescaling, FP64 Loewdin every 100 steps) gives the headline value; the FP64
+path is reported beside it with the deviation of the mixed path from it.  The
+JSON line also carries the roofline of the dominant kernel (the orbital
+propagation) and the CPU oracle timed on the host cores on a bounded sample of
+the same workload.
 
 Usage: python bench.py [--gpus 1] [--steps K] [--warmup W] [--no-cpu]
 """
@@ -39,13 +40,46 @@ if ROOT not in sys.path:
 PEAK_TFLOPS = {"fp64": 78.6, "mixed": 157.3}  # MI355X dense MFMA FP64 / FP32
 
 
-def prop_peak(path, dense=False):
-    """Roof of the propagation's algorithmic flops (TFLOP/s).  The mixed path's
-    arrowhead classes take three f16 products (2500 TFLOP/s) for one of FP32
-    accuracy; the dense kind takes FP32 ones.  The FP64 path's products on the
-    8-bit integer instructions are held against the FP64 peak, which they
-    may pass."""
-    return round(2500.0 / 3.0, 1) if path == "mixed" and not dense else PEAK_TFLOPS[path]
+F16_TFLOPS, I8_TOPS = 2500.0, 5000.0  # dense matrix peaks
+# 8-bit products for one of FP64 (M = 200, thermal velocities, dt = 20: the mean
+# over the 14 terms of the series)
+DIGIT_PAIRS = 16
+
+
+def prop_kernel(path, n, dense=False):
+    """The propagation kernel of a class (trajectories too fast for the two
+    latter ones take k_prop_queue, the instructions of k_prop)."""
+    if dense:
+        return "k_prop"
+    if path == "mixed":
+        return "k_prop_ip"
+    return "k_prop_i8" if (n + 15) // 16 >= 7 else "k_prop"
+
+
+def prop_peak(path, n, dense=False):
+    """Roof of the propagation's algorithmic flops (TFLOP/s) on the instructions
+    its kernel's products run on: k_prop_ip takes three f16 products for one of
+    FP32 accuracy, k_prop_i8 DIGIT_PAIRS 8-bit ones for one of FP64."""
+    kernel = prop_kernel(path, n, dense)
+    return round({"k_prop_ip": F16_TFLOPS / 3.0, "k_prop_i8": I8_TOPS / DIGIT_PAIRS,
+                  "k_prop": PEAK_TFLOPS[path]}[kernel], 1)
+
+
+def prop_roofline(path, n, tflops, dense=False):
+    """Common part of the propagation's roofline records."""
+    peak = prop_peak(path, n, dense)
+    kernel = prop_kernel(path, n, dense)
+    r = {"bound": "mfma", "kernel": kernel, "achieved": round(tflops, 3), "peak": peak, "unit": "TFLOP/s",
+         "frac": round(tflops / peak, 4)}
+    if kernel == "k_prop_i8":
+        r["fp64_matrix_peak"] = PEAK_TFLOPS["fp64"]
+    return r
+
+
+def prop_products(path, dense=False):
+    """What iesh_work counts: the products with the coupling matrix of a plan of
+    the interaction picture, or the series' terms."""
+    return "mean_products" if path == "mixed" and not dense else "mean_chebyshev_terms"
 
 
 HBM_PEAK_GBS = 8000.0
@@ -58,9 +92,22 @@ def algorithmic_prop_flops(n, N, sum_terms):
     return 4.0 * n * n * N * sum_terms
 
 
-def traffic_from_profile(path_md, kernel_src):
+PROP_SOURCES = {"k_prop": ["k_prop.hip"], "k_prop_ip": ["prop_ip.hpp", "k_prop.hip"],
+                "k_prop_i8": ["prop_i8.hpp", "k_prop.hip"]}
+
+
+def source_hash(kernel):
+    """SHA-256 of the sources a propagation kernel and its launch are built from."""
+    h = hashlib.sha256()
+    for f in PROP_SOURCES[kernel]:
+        h.update(open(os.path.join(ROOT, "paper_2212_00518_amd", "csrc", f), "rb").read())
+    return h.hexdigest()
+
+
+def traffic_from_profile(kernel, config):
     """HBM bytes per launch from a committed counter summary, if it was taken
-    on the current kernel source."""
+    on the current kernel sources."""
+    path_md = os.path.join(ROOT, "profiles", f"{kernel}_{config}_traffic.md")
     if not os.path.exists(path_md):
         return None
     text = open(path_md).read()
@@ -68,8 +115,7 @@ def traffic_from_profile(path_md, kernel_src):
     if not m:
         return None
     d = json.loads(m.group(1))
-    sha = hashlib.sha256(open(kernel_src, "rb").read()).hexdigest()
-    if d.get("kernel_source_sha256") != sha:
+    if d.get("kernel_source_sha256") != source_hash(kernel):
         return None
     return d.get("hbm_bytes_per_launch")
 
@@ -447,9 +493,7 @@ def scattering_run(steps, forced_lifetimes, n_traj=None, timed_steps=50, report_
     achieved = flops / (prop_ms * 1e-3) / 1e12 if prop_ms > 0 else 0.0
     return dict(cfg=cfg, T=T, classes=classes, wall=wall, traj_steps=traj_steps, visited=visited,
                 status=status, info0=info0, info1=info1, v_end=v_end, e_inc=e_inc, t_create=t_create,
-                roofline={"bound": "mfma", "kernel": "k_prop (all classes)", "achieved": round(achieved, 3),
-                          "peak": prop_peak("mixed"), "unit": "TFLOP/s",
-                          "frac": round(achieved / prop_peak("mixed"), 4), "traffic": None,
+                roofline={**prop_roofline("mixed", max(classes) + 1, achieved), "traffic": None,
                           "window_steps": timed_steps,
                           "prop_ms_per_step": round(prop_ms / timed_steps, 4)},
                 kernels_ms_per_step={k: round(v[0] / timed_steps, 4) for k, v in tm.items() if v[1]})
@@ -485,7 +529,7 @@ def scattering_bench(a):
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "f32+f64",
+        "dtype": "f32 (products in f16 pairs)+f64",
         "data": "synthetic",
         "config": {"workload": cfg["name"], "M_classes": classes, "n_traj": r["T"], "dt": cfg["dt"],
                    "forced_lifetimes": bool(a.forced_lifetimes), "path": "mixed"},
@@ -581,7 +625,7 @@ def desorption_bench(a):
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "f32+f64",
+        "dtype": "f32 (products in f16 pairs)+f64",
         "data": "synthetic",
         "config": {"workload": cfg["name"], "M": b["M"], "n_traj": T, "dt": cfg["dt"],
                    "kT": cfg["kT"], "Gamma": m["Gamma"], "path": "mixed",
@@ -620,7 +664,7 @@ def two_lead_bench(a):
         by_bias[f"{V:g}"] = {"value": round(r["value"], 2), "ms_per_step": round(r["ms_per_step"], 3),
                              "kernels_ms_per_launch": r["kernels_ms"],
                              "kernels_time_share": r["kernels_share"],
-                             "mean_chebyshev_terms": round(r["mean_cheb_terms"], 3),
+                             "mean_products": round(r["mean_cheb_terms"], 3),
                              "exact_hop_fraction": round(r["exact_hop_fraction"], 4),
                              "frozen": r["frozen"]}
     achieved = flops / (prop_ms * 1e-3) / 1e12 if prop_ms > 0 else 0.0
@@ -636,14 +680,12 @@ def two_lead_bench(a):
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "f32+f64",
+        "dtype": "f32 (products in f16 pairs)+f64",
         "data": "synthetic",
         "config": {"workload": cfg["name"], "n": n, "N": N, "n_traj": T, "dt": cfg["dt"],
                    "n_dof": len(cfg["model"]["dof"]), "bias": biases, "path": "mixed",
                    "elec_substeps": a.substeps},
-        "roofline": {"bound": "mfma", "achieved": round(achieved, 3), "peak": prop_peak("mixed"),
-                     "unit": "TFLOP/s", "frac": round(achieved / prop_peak("mixed"), 4),
-                     "traffic": None, "kernel": "k_prop",
+        "roofline": {**prop_roofline("mixed", n, achieved), "traffic": None,
                      "ms_per_launch": round(prop_ms / len(biases), 4)},
         "by_bias": by_bias,
     }
@@ -986,10 +1028,9 @@ def main():
                   file=sys.stderr, flush=True)
     head = "mixed" if "mixed" in res else "fp64"
     r = res[head]
-    src = os.path.join(ROOT, "paper_2212_00518_amd", "csrc", "k_prop.hip")
-    traffic = traffic_from_profile(os.path.join(ROOT, "profiles", f"k_prop_{head}_{a.config}_traffic.md"), src)
-    achieved = r["prop_tflops"]
     dense = cfg["model"].get("kind") == "dense"
+    n = cfg["bath"]["M"] + 1
+    traffic = traffic_from_profile(prop_kernel(head, n, dense), a.config)
     line = {
         # the headline metric on the headline workload; any other workload run
         # through this path names itself
@@ -1004,17 +1045,15 @@ def main():
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "f32+f64" if head == "mixed" else "f64",
+        "dtype": "f64" if head == "fp64" else "f32+f64" if dense else "f32 (products in f16 pairs)+f64",
         "data": "synthetic",
         "config": {"workload": cfg["name"], "M": cfg["bath"]["M"], "N": cfg["n_elec"],
                    "n_traj": T, "dt": cfg["dt"], "bath": cfg["bath"]["kind"], "path": head,
                    "elec_substeps": a.substeps, "dt_levels": a.dt_levels, "hop_gmax": a.hop_gmax},
-        "roofline": {"bound": "mfma", "achieved": round(achieved, 3), "peak": prop_peak(head, dense),
-                     "unit": "TFLOP/s", "frac": round(achieved / prop_peak(head, dense), 4),
-                     "traffic": traffic, "kernel": "k_prop",
+        "roofline": {**prop_roofline(head, n, r["prop_tflops"], dense), "traffic": traffic,
                      "flops_per_launch": r["prop_flops_per_launch"],
                      "ms_per_launch": round(r["prop_ms_per_launch"], 4),
-                     "mean_chebyshev_terms": round(r["mean_cheb_terms"], 3)},
+                     prop_products(head, dense): round(r["mean_cheb_terms"], 3)},
         "kernels_ms_per_launch": r["kernels_ms"],
         "kernels_time_share": r["kernels_share"],
         "exact_hop_fraction": round(r["exact_hop_fraction"], 4),
@@ -1023,11 +1062,10 @@ def main():
     if "fp64" in res and head != "fp64":
         f = res["fp64"]
         line["fp64"] = {"value": round(f["value"], 2), "ms_per_step": round(f["ms_per_step"], 3),
-                        "roofline": {"bound": "mfma", "achieved": round(f["prop_tflops"], 3),
-                                     "peak": PEAK_TFLOPS["fp64"], "unit": "TFLOP/s",
-                                     "frac": round(f["prop_tflops"] / PEAK_TFLOPS["fp64"], 4),
+                        "roofline": {**prop_roofline("fp64", n, f["prop_tflops"], dense),
+                                     "traffic": traffic_from_profile(prop_kernel("fp64", n, dense), a.config),
                                      "ms_per_launch": round(f["prop_ms_per_launch"], 4),
-                                     "mean_chebyshev_terms": round(f["mean_cheb_terms"], 3)},
+                                     prop_products("fp64", dense): round(f["mean_cheb_terms"], 3)},
                         "kernels_ms_per_launch": f["kernels_ms"],
                         "exact_hop_fraction": round(f["exact_hop_fraction"], 4)}
         line["mixed_over_fp64"] = round(r["value"] / f["value"], 3)
@@ -1038,7 +1076,7 @@ def main():
                 "value": round(r2["value"], 2), "ms_per_step": round(r2["ms_per_step"], 3),
                 "warmup": STEADY_WARMUP if not steady_window else a.warmup,
                 "steps": STEADY_STEPS if not steady_window else a.steps,
-                "roofline_frac": round(r2["prop_tflops"] / prop_peak(p, dense), 4),
+                "roofline_frac": round(r2["prop_tflops"] / prop_peak(p, n, dense), 4),
                 "prop_ms_per_launch": round(r2["prop_ms_per_launch"], 4),
                 "kernels_ms_per_launch": r2["kernels_ms"],
                 "kernels_time_share": r2["kernels_share"],

@@ -261,8 +261,9 @@ __device__ inline void jac_pair(int r, int k, int m, int& p, int& q) {
 // element to a neighbouring pair.  Then every thread updates 2x2 blocks of two
 // pairs a and b = a + d, d = 1 .. half/2, each unordered pair of pairs once.
 // Bound by the vector instructions of the blocks (about 80 each, a quarter of
-// them FP64), then by the rotations' serial chain.  The triangle's row offsets
-// are triangular numbers, which spread a column walk over all LDS banks.
+// them FP64) and the LDS (at n = 201 6,600 of 11,000 cycles a round, more than
+// half of them bank conflicts, though the triangular row offsets keep a column
+// walk off single banks), then by the rotations' serial chain.
 __device__ __forceinline__ void sweep_lds(const double* __restrict__ H, int n, double* Q, const JacWork& w, int b, int sweep,
                                           double* sm) {
   const int tid = threadIdx.x;

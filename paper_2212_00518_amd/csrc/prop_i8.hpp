@@ -20,7 +20,7 @@
 // steps the two errors' mean ratio was 1.002 up to there, 1.011 at 1/4 to 1/2,
 // 1.04 to 1, 1.09 to 2 and 1.2 to 4, where the 55 bits of B and b show.  Beyond
 // kMostProduct (fast trajectories, long steps) a trajectory's
-// products are left to the FP64 instructions (k_prop_queue).  At M = 200 a product takes 17 pairs of digits on average, and
+// products are left to the FP64 instructions (k_prop_queue).  At M = 200 a product takes 16 pairs of digits on average, and
 // the integer instructions do 64 for the time of one FP64 product.
 //
 // A work-group of W waves takes NCT tiles of 16 columns (8 orbitals as
@@ -35,8 +35,8 @@
 // the registers allow two waves to a SIMD, and the barrier keeps those of one
 // work-group in step.
 // One FP64 propagation of saturating batches, ms, FP64 instructions / this:
-// 2048 trajectories of M = 200 9.3 / 6.8, 512 of M = 120 0.56 / 0.37, 256 of
-// M = 320 4.9 / 2.5; of 16 trajectories of M = 100 0.098 / 0.046.
+// 2048 trajectories of M = 200 9.3 / 6.5, 512 of M = 120 0.56 / 0.36, 256 of
+// M = 320 4.9 / 2.4; of 16 trajectories of M = 100 0.098 / 0.046.
 #pragma once
 
 #include <type_traits>
@@ -417,9 +417,11 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 }
 
 // Classes that propagate this way: from 7 row tiles on, where the products
-// outweigh the rest.  Saturating batches, ms, FP64 instructions / digits: 5
-// row tiles 0.14 / 0.18, 6 0.25 / 0.26, 7 1.56 / 1.47, 8 0.56 / 0.37, 9 0.76 /
-// 0.65, 10 1.04 / 0.76; of 16 trajectories at 7 to 9 half the time.
+// outweigh the rest.  512 trajectories of N = M/2, thermal, dt = 20, ms, FP64
+// instructions / digits: 5 row tiles 0.195 / 0.254, 6 0.281 / 0.259 (at whose
+// gain the line is not worth moving), 7 0.430 / 0.358, 8 0.580 / 0.366, 9 0.814 /
+// 0.638, 10 1.10 / 0.74; 16 trajectories 0.061 / 0.045 at 5, 0.104 / 0.046 at 7.
+// Narrow classes gain least: 256 trajectories of M = 143, N = 17 lose 5% of a step.
 inline bool chosen(int n_pad) { return n_pad / 16 >= 7; }
 
 // Waves of a work-group, row tiles to a wave and orbital tiles to a work-group,

@@ -24,9 +24,11 @@
 // no exchange between lanes: the product's output, rounded, is the next
 // product's operand.
 //
-// Bound by the LDS: every wave reads all of M from it in each product (busy
-// 24% of the cycles in M's reads, 28% vector instructions, 21% matrix ones, two
-// waves to a SIMD).  Per step of a batch, ms, Chebyshev series / this with M
+// Bound by latency: at M = 200 a compute unit holds one work-group of seven
+// waves, which loads, multiplies and stores in turn (matrix instructions busy 27%
+// of the cycles, vector ones 35%, the LDS, from which every wave reads all of M
+// in each product, 31%; waves wait for 37% of their time), at M = 256 and 320 four
+// waves (19, 22 to 24 and 21%).  Per step of a batch, ms, Chebyshev series / this with M
 // in two buffers and its loads waited for before every LDS read / now:
 //   4096 trajectories, M = 200, N = 100                   5.53 / 1.26 / 1.08
 //   1536, two leads, M = 256, N = 128                     3.98 / 1.51 / 1.29
