@@ -19,9 +19,10 @@
 // a unit orbital (2^-7 for thermal trajectories at dt = 20): over 1040 emulated
 // steps the two errors' mean ratio was 1.002 up to there, 1.011 at 1/4 to 1/2,
 // 1.04 to 1, 1.09 to 2 and 1.2 to 4, where the 55 bits of B and b show.  Beyond
-// kMostProduct (fast trajectories, long steps) a trajectory's
-// products are left to the FP64 instructions (k_prop_queue).  At M = 200 a product takes 16 pairs of digits on average, and
-// the integer instructions do 64 for the time of one FP64 product.
+// kMostProduct (fast trajectories, long steps) a trajectory's products are left
+// to the FP64 instructions (k_prop_queue).  At M = 200 a product takes 16 pairs
+// of digits on average, and the integer instructions do 64 for the time of one
+// FP64 product.
 //
 // A work-group of W waves takes NCT tiles of 16 columns (8 orbitals as
 // [Re of 8 | Im of 8]); wave w has the row tiles w, w + W, ..  The digits of b
